@@ -17,7 +17,6 @@
 
 namespace peos {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct QueryTableArgs {
     const float* queries;  // nq x d

@@ -554,6 +554,30 @@ int peos_build_tables(const float* base, int64_t n, int32_t d, const int32_t* gr
                                 nullptr, index_mem, index_bytes, ws, ws_bytes, stream, out);
 }
 
+static void launch_edge_build(const peos::EdgeBuildArgs& a, bool compact, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.n + a.unit_nodes - 1) / a.unit_nodes)), block(64);
+    const size_t lds = peos::edge_build_lds(a.d, a.L);
+    const int mt = a.m / 16;
+    const bool full = (a.d / a.L) % 16 == 0;
+#define PEOS_BUILD(MT, C, S, F, P) \
+    hipLaunchKernelGGL((peos::k_edge_build<MT, C, S, F, P>), grid, block, lds, s, a)
+#define PEOS_BUILD_MT(C, F)                            \
+    if (mt == 1) PEOS_BUILD(1, C, false, F, false);    \
+    else if (mt == 2) PEOS_BUILD(2, C, false, F, false); \
+    else PEOS_BUILD(8, C, false, F, false);
+    // the optional forms share one instantiation each
+    if (a.sdirs) PEOS_BUILD(8, false, true, false, false);
+    else if (a.perm && compact) PEOS_BUILD(8, true, false, false, true);
+    else if (a.perm) PEOS_BUILD(8, false, false, false, true);
+    else if (compact && full) { PEOS_BUILD_MT(true, true) }
+    else if (compact) { PEOS_BUILD_MT(true, false) }
+    else if (full) { PEOS_BUILD_MT(false, true) }
+    else { PEOS_BUILD_MT(false, false) }
+#undef PEOS_BUILD_MT
+#undef PEOS_BUILD
+}
+
 int peos_build_tables_ex(const float* base, int64_t n, int32_t d, const int32_t* graph, int32_t R,
                          int32_t entry, int32_t L, int32_t m, const float* dirs_a,
                          const float* dirs_b, int32_t metric, int32_t flags,
@@ -607,9 +631,8 @@ int peos_build_tables_ex(const float* base, int64_t n, int32_t d, const int32_t*
     a.perm = perm;
     a.sdirs = (flags & PEOS_FLAG_SIMHASH) ? sdirs : nullptr;
     a.sig_off = l.sig_off;
-    a.compact = (flags & PEOS_FLAG_COMPACT) ? 1 : 0;
-    size_t lds = sizeof(float) * (size_t)(5 * d + 4 * L) + sizeof(int32_t) * (size_t)R * 4;
-    hipLaunchKernelGGL(peos::k_edge_build, dim3((unsigned)n), dim3(64), lds, s, a);
+    a.unit_nodes = R < 64 ? 64 / R : 1;
+    launch_edge_build(a, (flags & PEOS_FLAG_COMPACT) != 0, s);
     HIP_TRY(hipGetLastError());
     const int64_t bf16_off = (flags & PEOS_FLAG_BF16_BASE) ? round_up(n * l.stride, 256) : 0;
     if (flags & PEOS_FLAG_BF16_BASE) {

@@ -6,6 +6,8 @@
 
 namespace peos {
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
 constexpr int kWave = 64;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // empty visited-hash slot
 constexpr uint32_t kExpanded = 0x80000000u; // "expanded" flag on a list id
