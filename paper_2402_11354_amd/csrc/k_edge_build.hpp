@@ -46,6 +46,11 @@
 // then wait in LDS in step order (each is used by the codes, the norms and
 // the residual), kSegment coordinates at a time, longer vectors being
 // gathered again for the residual.
+// Measured: 400,000 nodes of degree 32 at d = 128, L = 8, m = 16 (no perm)
+// 86.8 -> 3.1 ms (one fma per operand load before; now the vector ALUs are
+// busy half the time, the matrix cores 22%, and a wave waits on its gather
+// 44% of its cycles at 3 waves a SIMD); 20,000 nodes at d = 960, L = 16 27.9
+// -> 2.2 ms (55% waiting: two passes over 17 KB segments at 2 waves a SIMD).
 #pragma once
 
 #include <type_traits>
@@ -74,100 +79,160 @@ struct EdgeBuildArgs {
 };
 
 constexpr int kCompactZeroEdge = 255;
-// coordinates of the 16 edges' vectors held in LDS at a time (a multiple of
-// 64, so that every coordinate keeps its place mod 16): 17 KB a wave at 256,
-// eight waves a CU for long vectors; up to 256 coordinates are gathered once
+// Coordinates of the 16 edges' vectors held in LDS at a time (a multiple of 16,
+// so that every coordinate keeps its place mod 16): vectors of up to 256 are
+// held whole and gathered once, 9 KB a wave at d = 128 and so 13 waves a CU;
+// longer ones go by whole groups of four blocks, around 256 coordinates (17 KB,
+// eight waves a CU), when a group is at most 512, else by 256 wherever the
+// blocks lie.
 constexpr int kSegment = 256;
+constexpr int kMaxGroup = 512;
 constexpr int kChunkWords = 4 * 64 + 16;  // LDS words of 16 coordinates: four steps of 64
                                           // lanes, padded so that lanes four steps apart
                                           // (the block norms) use different banks
 constexpr int kCodeRow = 36;              // code bytes of one edge, at most
 
-inline size_t edge_build_lds(int d, int L)
+// the codes are taken four blocks at a time
+__host__ __device__ inline bool edge_build_groups(int d, int L, int m)
 {
-    const int seg = d < kSegment ? (d + 15) / 16 * 16 : kSegment;
-    return sizeof(float) * ((size_t)(seg / 16) * kChunkWords + 16 * (size_t)L + 5 * 64) + 16 * kCodeRow;
+    // (with more than two direction tiles a block's own chains fill the
+    // matrix cores, and four blocks' would not fit the registers)
+    return m <= 32 && (L < 4 ? d : 4 * (d / L)) <= kMaxGroup;
+}
+
+__host__ __device__ inline int edge_build_segment(int d, int L, bool groups)
+{
+    if (d <= kSegment || (groups && L < 4)) return (d + 15) / 16 * 16;
+    if (!groups) return kSegment;
+    const int group = 4 * (d / L);
+    return group > kSegment ? group : kSegment / group * group;
+}
+
+inline size_t edge_build_lds(int d, int L, bool groups)
+{
+    const int seg = edge_build_segment(d, L, groups);
+    return sizeof(float) * ((size_t)(seg / 16) * kChunkWords + 16 * (size_t)L + 7 * 64) + 16 * kCodeRow;
+}
+
+// row (16-lane group) swaps of two registers: the odd rows of a with the even
+// rows of b, and the upper half of a with the lower half of b
+template <typename T>
+__device__ __forceinline__ void swap_rows(T& a, T& b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]);
+    b = __builtin_bit_cast(T, (uint32_t)r[1]);
+}
+
+template <typename T>
+__device__ __forceinline__ void swap_halves(T& a, T& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]);
+    b = __builtin_bit_cast(T, (uint32_t)r[1]);
 }
 
 // 4 x 4 transpose between the four groups of 16 lanes and four registers:
 // afterwards register c of group g holds what register g of group c held
 __device__ __forceinline__ void transpose4(float (&x)[4])
 {
-    auto swap32 = [](float& a, float& b) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-        a = __uint_as_float(r[0]);
-        b = __uint_as_float(r[1]);
-    };
-    auto swap16 = [](float& a, float& b) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-        a = __uint_as_float(r[0]);
-        b = __uint_as_float(r[1]);
-    };
-    swap32(x[0], x[2]);
-    swap32(x[1], x[3]);
-    swap16(x[0], x[1]);
-    swap16(x[2], x[3]);
+    swap_halves(x[0], x[2]);
+    swap_halves(x[1], x[3]);
+    swap_rows(x[0], x[1]);
+    swap_rows(x[2], x[3]);
 }
 
 // LDS word of step t (coordinates 4t .. 4t + 3 of the segment)
 __device__ __forceinline__ int step_word(int t) { return (t >> 2) * kChunkWords + (t & 3) * 64; }
 
-// The code of each edge (lane % 16) from its m products: the first largest
-// |p|, plus m if that p is negative.  acc[t][r] is direction 16 t + 4 g + r.
-template <int MT>
-__device__ __forceinline__ int extreme_code(const floatx4 (&acc)[MT], int mt, int m, int g)
+// An extreme product and its direction.  A larger |p| wins, ties go to the
+// smaller direction, and a NaN loses to any number.
+struct Extreme {
+    float p;
+    int j;
+};
+
+__device__ __forceinline__ Extreme extreme_of(Extreme a, Extreme b)
 {
-    float best = -1.f;
-    int code = 0;  // direction, plus 256 if its product is negative
+    const bool second = (fabsf(b.p) > fabsf(a.p)) | ((fabsf(b.p) == fabsf(a.p)) & (b.j < a.j)) | (a.p != a.p);
+    return Extreme{second ? b.p : a.p, second ? b.j : a.j};
+}
+
+// this lane's extreme of one edge: acc[t][r] is direction 16 t + 4 g + r
+template <int MT>
+__device__ __forceinline__ Extreme lane_extreme(const floatx4* acc, int mt, int g)
+{
+    Extreme x{acc[0][0], 4 * g};
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         if (t >= mt) break;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
+            if (t == 0 && r == 0) continue;
             const float p = acc[t][r];
-            const bool up = fabsf(p) > best;
-            best = up ? fabsf(p) : best;
-            code = up ? 16 * t + 4 * g + r + (p < 0.f ? 256 : 0) : code;
+            const bool up = (fabsf(p) > fabsf(x.p)) | (x.p != x.p);  // (directions ascend: no ties to settle)
+            x = Extreme{up ? p : x.p, up ? 16 * t + 4 * g + r : x.j};
         }
     }
-    auto fold = [&](float b0, int c0, float b1, int c1) {
-        const bool second = (b1 > b0) | ((b1 == b0) & ((c1 & 255) < (c0 & 255)));
-        best = second ? b1 : b0;
-        code = second ? c1 : c0;
+    return x;
+}
+
+// the code byte: the direction, plus m if its product is negative
+__device__ __forceinline__ int code_of(Extreme x, int m) { return x.p != x.p ? 0 : x.j + (x.p < 0.f ? m : 0); }
+
+// the extreme over the four lane groups, in every lane
+__device__ __forceinline__ Extreme group_extreme(Extreme x)
+{
+    Extreme y = x;
+    swap_rows(x.p, y.p);
+    swap_rows(x.j, y.j);
+    x = y = extreme_of(x, y);
+    swap_halves(x.p, y.p);
+    swap_halves(x.j, y.j);
+    return extreme_of(x, y);
+}
+
+// the same for four blocks at once: lane group g receives block g's
+__device__ __forceinline__ Extreme group_extreme4(Extreme (&x)[4])
+{
+    auto fold = [](Extreme& a, Extreme& b, auto swap) {
+        swap(a.p, b.p);
+        swap(a.j, b.j);
+        return extreme_of(a, b);
     };
-    {
-        const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(best), __float_as_uint(best), false, false);
-        const auto c = __builtin_amdgcn_permlane16_swap((uint32_t)code, (uint32_t)code, false, false);
-        fold(__uint_as_float(b[0]), (int)c[0], __uint_as_float(b[1]), (int)c[1]);
-    }
-    {
-        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(best), __float_as_uint(best), false, false);
-        const auto c = __builtin_amdgcn_permlane32_swap((uint32_t)code, (uint32_t)code, false, false);
-        fold(__uint_as_float(b[0]), (int)c[0], __uint_as_float(b[1]), (int)c[1]);
-    }
-    return (code & 255) + (code >= 256 ? m : 0);
+    auto rows = [](auto& a, auto& b) { swap_rows(a, b); };
+    auto halves = [](auto& a, auto& b) { swap_halves(a, b); };
+    Extreme lo = fold(x[0], x[1], rows), hi = fold(x[2], x[3], rows);
+    return fold(lo, hi, halves);
 }
 
 // MT: 16-direction tiles, at least m / 16 (exactly, up to 2).  FULL: blocks are
 // whole groups of four steps (d / L a multiple of 16), so no chunk of a block
-// or a vector is partly filled.  PERM: with a dimension permutation.
-template <int MT, bool COMPACT, bool SIM, bool FULL, bool PERM>
-__global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
+// or a vector is partly filled.  GROUP: codes four blocks at a time (see
+// edge_build_groups).  PERM: with a dimension permutation.
+template <int MT, bool COMPACT, bool SIM, bool FULL, bool PERM, bool GROUP>
+__global__ __launch_bounds__(64, MT <= 2 ? 4 : 3) void k_edge_build(EdgeBuildArgs a)
 {
 #pragma clang fp contract(off)
     extern __shared__ __align__(16) float smem[];
     const int d = a.d, R = a.R, L = a.L, m = a.m;
     const int dp = d / L;
     const int mt = MT <= 2 ? MT : m >> 4;
-    const int seg = d < kSegment ? (d + 15) / 16 * 16 : kSegment;
+    const int seg = edge_build_segment(d, L, GROUP);
     float* et = smem;                                // the tile's edge vectors, in step order
     float* sb = et + (seg / 16) * kChunkWords;       // 16 x L block norms (compact: squared)
     int32_t* row = reinterpret_cast<int32_t*>(sb + 16 * L);  // the unit's neighbour ids
     float* nvs = reinterpret_cast<float*>(row + 64);         // |v|^2 per node of the unit
-    float* cgp = nvs + 64;                           // compact: scalars and kind per edge
-    float* cie = cgp + 64;
-    int32_t* ckd = reinterpret_cast<int32_t*>(cie + 64);
-    uint8_t* cb = reinterpret_cast<uint8_t*>(ckd + 64);
+    // per edge of the unit, for the scalars at the end.  Compact: g_e/|e|,
+    // 1/|e| and the kind; full: |u|^2, |e|^2, |e_res|^2, c, L'
+    float* ea = nvs + 64;
+    float* eb = ea + 64;
+    float* ecn = eb + 64;
+    float* ed = ecn + 64;
+    int32_t* ei = reinterpret_cast<int32_t*>(ed + 64);
+    uint8_t* cb = reinterpret_cast<uint8_t*>(ei + 64);  // 16 x kCodeRow: the tile's codes
     const int lane = lane_id();
     const int g = lane >> 4;    // lane group: K offset within an MFMA step
     const int ec = lane & 15;   // edge of the tile (and direction row of the other operand)
@@ -175,11 +240,13 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
     const int64_t v0 = (int64_t)blockIdx.x * a.unit_nodes;
     const int nn = (int)(a.n - v0 < a.unit_nodes ? a.n - v0 : a.unit_nodes);
     const int E = nn * R;
+    const uint32_t inv_r = (65535u + (uint32_t)R) / (uint32_t)R;
+    auto node_of = [&](int f) { return (int)(((uint32_t)f * inv_r) >> 16); };  // f / R for f < 64
     if (lane < E) row[lane] = a.graph[v0 * R + lane];
     wave_sync();
     // graph validation: id range, self loop, repeated id in the row
     if (lane < E) {
-        const int b = lane / R;
+        const int b = node_of(lane);
         const int32_t u = row[lane];
         bool bad = (u < -1) || (u >= a.n) || (u == v0 + b);
         for (int jj = 0; jj < R; ++jj) bad |= b * R + jj < lane && u >= 0 && row[b * R + jj] == u;
@@ -217,16 +284,24 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
         if (!PERM) return *reinterpret_cast<const float4*>(x + k);
         return make_float4(x[a.perm[k]], x[a.perm[k + 1]], x[a.perm[k + 2]], x[a.perm[k + 3]]);
     };
-    // four steps (coordinates k .. k + 15) of a direction tile, in step order
-    // (zeros from kend on)
-    auto dirs4 = [&](const float* p, int k, int kend, float (&x)[4]) {
-        const bool in = FULL || k + 4 * g < kend;
-        const float4 v = *reinterpret_cast<const float4*>(p + (in ? k + 4 * g : 0));
+    // four steps (coordinates k .. k + 15) of a tile of 16 directions of
+    // `len` coordinates each, in step order (zeros from len on)
+    auto dirs4 = [&](const float* dirs, int k, int len, float (&x)[4]) {
+        const bool in = FULL || k + 4 * g < len;
+        const float4 v = *reinterpret_cast<const float4*>(dirs + (uint32_t)(ec * len + (in ? k + 4 * g : 0)));
         x[0] = in ? v.x : 0.f;
         x[1] = in ? v.y : 0.f;
         x[2] = in ? v.z : 0.f;
         x[3] = in ? v.w : 0.f;
         transpose4(x);
+    };
+    // the edges' vectors at four steps from coordinate k of the segment
+    auto edges4 = [&](int k, int ns, float (&e)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int w = FULL ? (k >> 4) * kChunkWords + 64 * c : step_word((k >> 2) + c);
+            e[c] = c < ns ? et[w + lane] : 0.f;
+        }
     };
 
     const int ntile = (E + 15) >> 4;
@@ -235,7 +310,7 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
         int32_t u = f < E ? row[f] : -1;
         if (u >= a.n) u = -1;  // never dereferenced (reported through err)
         const bool ok = u >= 0;
-        const int b = f < E ? f / R : 0;
+        const int b = f < E ? node_of(f) : 0;
         const float* xv = a.base + (v0 + b) * d;
         const float* xu = ok ? a.base + (int64_t)u * d : xv;  // no edge: e = 0
 
@@ -275,6 +350,10 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
         };
         auto stage = [&](int k0, int len, bool first) {
             int k = 0;
+            if (PERM) {  // (a coordinate at a time: fewer in flight)
+                for (; k < len; k += 16) chunks(std::integral_constant<int, 1>(), k0, k, len, first);
+                return;
+            }
             for (; k + 128 <= len; k += 128) chunks(std::integral_constant<int, 8>(), k0, k, len, first);
             if (len - k > 48) {
                 chunks(std::integral_constant<int, 4>(), k0, k, len, first);
@@ -317,32 +396,74 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
                 sb[ec * L + i] = (!COMPACT && ke == (i + 1) * dp) ? sqrtf(ss) : ss;
             }
             // subspace codes
-            for (int i = i0; i <= i1; ++i) {
-                const int kb = i * dp > k0 ? i * dp : k0;
-                const int ke = (i + 1) * dp < k0 + len ? (i + 1) * dp : k0 + len;
-                if (kb == i * dp) {
+            if (GROUP) {
+                // segments hold whole groups: four blocks' chains side by
+                // side, then one exchange for the four extremes
+                for (int ig = i0; ig <= i1; ig += 4) {
+                    Extreme x4[4];
+                    constexpr int Q = MT == 1 ? 4 : 1;  // chains side by side in one tile
 #pragma unroll
-                    for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-                }
-                const float* av = a.dirs_a + ((int64_t)i * m + ec) * dp;
-                for (int k = kb; k < ke; k += 16) {
-                    const int ns = !FULL && ke - k < 16 ? (ke - k) >> 2 : 4;
-                    float e[4];
+                    for (int q0 = 0; q0 < 4; q0 += Q) {
+                        floatx4 ac[Q][MT];
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) e[c] = c < ns ? et[step_word(((k - k0) >> 2) + c) + lane] : 0.f;
+                        for (int q = 0; q < Q; ++q)
 #pragma unroll
-                    for (int t = 0; t < MT; ++t) {
-                        if (t >= mt) break;
-                        float x[4];
-                        dirs4(av + (int64_t)t * 16 * dp, k - i * dp, dp, x);
+                            for (int t = 0; t < MT; ++t) ac[q][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        for (int ks = 0; ks < dp; ks += 16) {
+                            const int ns = !FULL && dp - ks < 16 ? (dp - ks) >> 2 : 4;
+                            float e[Q][4], x[Q][MT][4];
 #pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            if (c < ns) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], e[c], acc[t], 0, 0, 0);
+                            for (int q = 0; q < Q; ++q) {
+                                const int i = ig + q0 + q <= i1 ? ig + q0 + q : i1;
+#pragma unroll
+                                for (int t = 0; t < MT; ++t)
+                                    if (t < mt) dirs4(a.dirs_a + ((int64_t)i * m + 16 * t) * dp, ks, dp, x[q][t]);
+                                edges4(i * dp - k0 + ks, ns, e[q]);
+                            }
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                if (c >= ns) break;
+#pragma unroll
+                                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                                    for (int t = 0; t < MT; ++t)
+                                        if (t < mt)
+                                            ac[q][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][t][c], e[q][c],
+                                                                                            ac[q][t], 0, 0, 0);
+                            }
+                        }
+#pragma unroll
+                        for (int q = 0; q < Q; ++q) x4[q0 + q] = lane_extreme<MT>(ac[q], mt, g);
                     }
+                    const int code = code_of(group_extreme4(x4), m);
+                    if (ig + g <= i1) cb[ec * kCodeRow + cfirst + ig + g] = ok ? (uint8_t)code : 0;
                 }
-                if (ke == (i + 1) * dp) {
-                    const int code = extreme_code<MT>(acc, mt, m, g);
-                    if (g == 0) cb[ec * kCodeRow + cfirst + i] = ok ? (uint8_t)code : 0;
+            } else {
+                for (int i = i0; i <= i1; ++i) {
+                    const int kb = i * dp > k0 ? i * dp : k0;
+                    const int ke = (i + 1) * dp < k0 + len ? (i + 1) * dp : k0 + len;
+                    if (kb == i * dp) {
+#pragma unroll
+                        for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+                    for (int k = kb; k < ke; k += 16) {
+                        const int ns = ke - k < 16 ? (ke - k) >> 2 : 4;
+                        float e[4];
+                        edges4(k - k0, ns, e);
+#pragma unroll
+                        for (int t = 0; t < MT; ++t) {
+                            if (t >= mt) break;
+                            float x[4];
+                            dirs4(a.dirs_a + ((int64_t)i * m + 16 * t) * dp, k - i * dp, dp, x);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (c < ns) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], e[c], acc[t], 0, 0, 0);
+                        }
+                    }
+                    if (ke == (i + 1) * dp) {
+                        const int code = code_of(group_extreme(lane_extreme<MT>(acc, mt, g)), m);
+                        if (g == 0) cb[ec * kCodeRow + cfirst + i] = ok ? (uint8_t)code : 0;
+                    }
                 }
             }
             if (SIM) {
@@ -353,7 +474,7 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         float x[4];
-                        dirs4(a.sdirs + (int64_t)(16 * t + ec) * d, k0 + k, d, x);
+                        dirs4(a.sdirs + (int64_t)(16 * t) * d, k0 + k, d, x);
 #pragma unroll
                         for (int c = 0; c < 4; ++c)
                             if (c < ns)
@@ -396,9 +517,9 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
                         ie = 1.f / nrm;
                     }
                 }
-                cgp[f] = gp;
-                cie[f] = ie;
-                ckd[f] = kd;
+                ea[f] = gp;
+                eb[f] = ie;
+                ei[f] = kd;
                 uint32_t w = 0u;
                 for (int i = 0; i < L; ++i) w |= (uint32_t)cb[ec * kCodeRow + i] << (8 * i);
                 *reinterpret_cast<uint32_t*>(rv + a.codes_off + 4 * j) = w;
@@ -433,6 +554,13 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
             nz += s > 0.f;
         }
         c = nz > 0 ? ssum / (float)nz : 0.f;
+        // c / s_i, each lane group every fourth block, in place of the norms
+        wave_sync();
+        for (int i = g; i < L; i += 4) {
+            const float s = sb[ec * L + i];
+            sb[ec * L + i] = s > 0.f ? c / s : 0.f;
+        }
+        wave_sync();
 
         // residual e - (c / s_i) e and its code, four steps at a time
         float nr[4] = {0.f, 0.f, 0.f, 0.f};
@@ -457,8 +585,7 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
                         continue;
                     }
                     if ((!FULL || q == 0) && k0 + k + 4 * q == bnd) {
-                        const float s = sb[ec * L + blk];
-                        ratio = s > 0.f ? c / s : 0.f;
+                        ratio = sb[ec * L + blk];
                         ++blk;
                         bnd += dp;
                     }
@@ -470,14 +597,14 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
                 for (int t = 0; t < MT; ++t) {
                     if (t >= mt) break;
                     float x[4];
-                    dirs4(a.dirs_b + (int64_t)(16 * t + ec) * d, k0 + k, d, x);
+                    dirs4(a.dirs_b + (int64_t)(16 * t) * d, k0 + k, d, x);
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         if (q < ns) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], e[q], acc[t], 0, 0, 0);
                 }
             }
         }
-        const int rcode = extreme_code<MT>(acc, mt, m, g);
+        const int rcode = code_of(group_extreme(lane_extreme<MT>(acc, mt, g)), m);
         if (g == 0) {
             cb[ec * kCodeRow] = ok ? (uint8_t)rcode : 0;
             for (int pz = L + 1; pz < cbytes; ++pz) cb[ec * kCodeRow + pz] = 0;
@@ -496,80 +623,82 @@ __global__ __launch_bounds__(64) void k_edge_build(EdgeBuildArgs a)
             nu[q] += xor_lane<32>(nu[q]);
             nu[q] += xor_lane<16>(nu[q]);
         }
-        const float nu2 = (nu[0] + nu[2]) + (nu[1] + nu[3]);
-        // scalars: g_e, |e|, w_reg, sqrt(L) w_res; in the precision form
-        // the halves of g_e/|e|, 1/|e| (infinite for a zero edge), w_reg,
-        // sqrt(L) w_res
         if (g == 0 && f < E) {
-            float ge = 0.f, en = 0.f, wreg = 0.f, swres = 0.f;
-            if (ok) {
-                en = sqrtf(ne2);
-                if (en > 0.f) {
-                    wreg = fminf(1.f, c * sqrtf((float)nz) / en);
-                    swres = sqrtf((float)L) * fminf(1.f, sqrtf(nr2) / en);
-                } else {
-                    wreg = 1.f;
-                    swres = 0.f;
-                }
-                if (a.metric == 0) ge = 0.5f * (nu2 - nvs[b]);
-            }
-            if (a.half_scalars) {
-                const float gp = en > 0.f ? ge / en : 0.f;
-                const float ie = en > 0.f ? 1.f / en : INFINITY;
-                _Float16* hs = reinterpret_cast<_Float16*>(rv + a.scal_off) + 4 * j;
-                hs[0] = (_Float16)(ok ? gp : 0.f);
-                hs[1] = (_Float16)(ok ? ie : 0.f);
-                hs[2] = (_Float16)wreg;
-                hs[3] = (_Float16)swres;
-            } else {
-                *reinterpret_cast<float4*>(reinterpret_cast<float*>(rv + a.scal_off) + 4 * j) =
-                    make_float4(ge, en, wreg, swres);
-            }
+            ea[f] = (nu[0] + nu[2]) + (nu[1] + nu[3]);
+            eb[f] = ne2;
+            ecn[f] = nr2;
+            ed[f] = c;
+            ei[f] = ok ? nz : -1;
         }
-        // the codes, a dword per lane
+        // the codes: lane group g stores every fourth dword of its edge
         wave_sync();
-        const int cwords = cbytes >> 2;
-        for (int w = lane; w < 16 * cwords; w += kWave) {
-            const int e = w / cwords, o = w - e * cwords;
-            const int fe = 16 * T + e;
-            if (fe >= E) break;
-            const int be = fe / R;
-            *reinterpret_cast<uint32_t*>(a.rec + (v0 + be) * a.node_stride + a.codes_off +
-                                         (int64_t)(fe - be * R) * cbytes + 4 * o) =
-                *reinterpret_cast<const uint32_t*>(cb + e * kCodeRow + 4 * o);
-        }
+        if (f < E)
+            for (int w = g; w < cbytes >> 2; w += 4)
+                *reinterpret_cast<uint32_t*>(rv + a.codes_off + (int64_t)j * cbytes + 4 * w) =
+                    *reinterpret_cast<const uint32_t*>(cb + ec * kCodeRow + 4 * w);
     }
-    if (!COMPACT) return;
-    // compact: node ranges (min / max are exact in any order) and the codes
     wave_sync();
     if (lane >= E) return;
-    const int b = lane / R;
+    const int b = node_of(lane), j = lane - b * R;
+    uint8_t* rv = a.rec + (v0 + b) * a.node_stride;
+    if (!COMPACT) {
+        // scalars of the unit's edges, one per lane: g_e, |e|, w_reg, sqrt(L)
+        // w_res; in the precision form the halves of g_e/|e|, 1/|e| (infinite
+        // for a zero edge), w_reg, sqrt(L) w_res
+        float ge = 0.f, en = 0.f, wreg = 0.f, swres = 0.f;
+        const int nz = ei[lane];
+        const bool ok = nz >= 0;
+        if (ok) {
+            en = sqrtf(eb[lane]);
+            if (en > 0.f) {
+                wreg = fminf(1.f, ed[lane] * sqrtf((float)nz) / en);
+                swres = sqrtf((float)L) * fminf(1.f, sqrtf(ecn[lane]) / en);
+            } else {
+                wreg = 1.f;
+                swres = 0.f;
+            }
+            if (a.metric == 0) ge = 0.5f * (ea[lane] - nvs[b]);
+        }
+        if (a.half_scalars) {
+            const float gp = en > 0.f ? ge / en : 0.f;
+            const float ie = en > 0.f ? 1.f / en : INFINITY;
+            _Float16* hs = reinterpret_cast<_Float16*>(rv + a.scal_off) + 4 * j;
+            hs[0] = (_Float16)(ok ? gp : 0.f);
+            hs[1] = (_Float16)(ok ? ie : 0.f);
+            hs[2] = (_Float16)wreg;
+            hs[3] = (_Float16)swres;
+        } else {
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(rv + a.scal_off) + 4 * j) =
+                make_float4(ge, en, wreg, swres);
+        }
+        return;
+    }
+    // compact: node ranges (min / max are exact in any order) and the codes
     float glo = INFINITY, ghi = -INFINITY, ilo = INFINITY, ihi = -INFINITY;
-    for (int j = b * R; j < (b + 1) * R; ++j) {
-        if (ckd[j] != 1) continue;
-        glo = fminf(glo, cgp[j]);
-        ghi = fmaxf(ghi, cgp[j]);
-        ilo = fminf(ilo, cie[j]);
-        ihi = fmaxf(ihi, cie[j]);
+    for (int t = b * R; t < (b + 1) * R; ++t) {
+        if (ei[t] != 1) continue;
+        glo = fminf(glo, ea[t]);
+        ghi = fmaxf(ghi, ea[t]);
+        ilo = fminf(ilo, eb[t]);
+        ihi = fmaxf(ihi, eb[t]);
     }
     if (!(glo <= ghi)) glo = ghi = ilo = ihi = 0.f;  // no edge of nonzero length
     const float gstep = (ghi - glo) / 255.f;
     const float istep = (ihi - ilo) / 254.f;
-    uint8_t* rv = a.rec + (v0 + b) * a.node_stride;
-    if (lane == b * R) *reinterpret_cast<float4*>(rv) = make_float4(glo, gstep, ilo, istep);
+    if (j == 0) *reinterpret_cast<float4*>(rv) = make_float4(glo, gstep, ilo, istep);
     uint32_t cg = 0u, ci = 0u;
-    if (ckd[lane] == 2) ci = kCompactZeroEdge;
-    if (ckd[lane] == 1) {
+    if (ei[lane] == 2) ci = kCompactZeroEdge;
+    if (ei[lane] == 1) {
         if (gstep > 0.f) {
-            const float c = floorf((cgp[lane] - glo) / gstep);
+            const float c = floorf((ea[lane] - glo) / gstep);
             cg = (uint32_t)(c < 0.f ? 0.f : (c > 255.f ? 255.f : c));
         }
         if (istep > 0.f) {
-            const float c = rintf((cie[lane] - ilo) / istep);
+            const float c = rintf((eb[lane] - ilo) / istep);
             ci = (uint32_t)(c < 0.f ? 0.f : (c > 254.f ? 254.f : c));
         }
     }
-    reinterpret_cast<uint16_t*>(rv + a.scal_off)[lane - b * R] = (uint16_t)(cg | (ci << 8));
+    reinterpret_cast<uint16_t*>(rv + a.scal_off)[j] = (uint16_t)(cg | (ci << 8));
 }
 
 // Energy of the edge coordinates for the optional dimension permutation:

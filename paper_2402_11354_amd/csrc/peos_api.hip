@@ -557,19 +557,18 @@ int peos_build_tables(const float* base, int64_t n, int32_t d, const int32_t* gr
 static void launch_edge_build(const peos::EdgeBuildArgs& a, bool compact, hipStream_t s)
 {
     const dim3 grid((unsigned)((a.n + a.unit_nodes - 1) / a.unit_nodes)), block(64);
-    const size_t lds = peos::edge_build_lds(a.d, a.L);
-    const int mt = a.m / 16;
+    const bool groups = !a.sdirs && !a.perm && peos::edge_build_groups(a.d, a.L, a.m);
     const bool full = (a.d / a.L) % 16 == 0;
-#define PEOS_BUILD(MT, C, S, F, P) \
-    hipLaunchKernelGGL((peos::k_edge_build<MT, C, S, F, P>), grid, block, lds, s, a)
-#define PEOS_BUILD_MT(C, F)                            \
-    if (mt == 1) PEOS_BUILD(1, C, false, F, false);    \
-    else if (mt == 2) PEOS_BUILD(2, C, false, F, false); \
-    else PEOS_BUILD(8, C, false, F, false);
-    // the optional forms share one instantiation each
-    if (a.sdirs) PEOS_BUILD(8, false, true, false, false);
-    else if (a.perm && compact) PEOS_BUILD(8, true, false, false, true);
-    else if (a.perm) PEOS_BUILD(8, false, false, false, true);
+    const size_t lds = peos::edge_build_lds(a.d, a.L, groups);
+#define PEOS_BUILD(MT, C, S, F, P, G) \
+    hipLaunchKernelGGL((peos::k_edge_build<MT, C, S, F, P, G>), grid, block, lds, s, a)
+#define PEOS_BUILD_MT(C, F)                                   \
+    if (!groups) PEOS_BUILD(8, C, false, F, false, false);    \
+    else if (a.m == 16) PEOS_BUILD(1, C, false, F, false, true); \
+    else PEOS_BUILD(2, C, false, F, false, true);
+    if (a.sdirs) PEOS_BUILD(8, false, true, false, false, false);
+    else if (a.perm && compact) PEOS_BUILD(8, true, false, false, true, false);
+    else if (a.perm) PEOS_BUILD(8, false, false, false, true, false);
     else if (compact && full) { PEOS_BUILD_MT(true, true) }
     else if (compact) { PEOS_BUILD_MT(true, false) }
     else if (full) { PEOS_BUILD_MT(false, true) }

@@ -39,7 +39,9 @@ def inputs(n, d, R, L, m):
 
 
 SHAPES = [(97, 4, 1, 1, 16), (150, 20, 17, 5, 48), (130, 96, 33, 12, 32), (90, 260, 48, 5, 16),
-          (70, 516, 64, 3, 128), (41, 960, 20, 16, 16), (66, 128, 32, 32, 16), (3, 64, 16, 4, 16)]
+          (70, 516, 64, 3, 128), (41, 960, 20, 16, 16), (66, 128, 32, 32, 16), (3, 64, 16, 4, 16),
+          (70, 128, 32, 8, 16), (70, 128, 33, 4, 32), (40, 320, 31, 5, 16), (60, 128, 32, 8, 128),
+          (45, 480, 24, 6, 32)]
 
 
 @pytest.mark.parametrize("perm", [False, True])
@@ -69,7 +71,8 @@ def test_records_at_tile_edges(shape, perm):
 
 @pytest.mark.parametrize("perm", [False, True])
 @pytest.mark.parametrize("shape", [(97, 4, 1, 1, 16), (130, 96, 33, 3, 32), (90, 260, 48, 1, 16),
-                                   (70, 516, 64, 3, 128), (150, 16, 17, 4, 48)], ids=str)
+                                   (70, 516, 64, 3, 128), (150, 16, 17, 4, 48),
+                                   (70, 128, 32, 2, 16), (60, 64, 32, 4, 32)], ids=str)
 def test_compact_records_at_tile_edges(shape, perm):
     n, d, R, L, m = shape
     x, g, A, B = inputs(*shape)
