@@ -64,7 +64,7 @@ __global__ __launch_bounds__(64) void k_descend(DescendArgs a)
                 const uint64_t mk = ballot(valid);
                 const int ns = popc(mk);
                 if (valid) {
-                    const int pos = popc(mk & lanemask_lt());
+                    const int pos = lanes_before(mk);
                     Su[pos] = (uint32_t)a.node[nb];
                     Srow[pos] = nb;
                 }

@@ -104,14 +104,17 @@ __device__ __forceinline__ bool has_key(uint4 k, uint32_t u)
     return k.x == u || k.y == u || k.z == u || k.w == u;
 }
 
-__device__ __forceinline__ bool hash_lookup(const uint32_t* h, uint32_t cap, uint32_t u)
+// free: the slot an insert of u would take by these reads (-1: both full)
+__device__ __forceinline__ bool hash_lookup(const uint32_t* h, uint32_t cap, uint32_t u, int& free)
 {
     const uint32_t nb = cap >> 2;
     const uint32_t b1 = hash_bucket(u, nb), b2 = hash_bucket2(u, nb);
     const uint4 k1 = reinterpret_cast<const uint4*>(h)[b1];
     const uint4 k2 = reinterpret_cast<const uint4*>(h)[b2];
+    const int f1 = free_slots(k1), f2 = free_slots(k2);
+    free = (f1 | f2) == 0 ? -1 : (f2 > f1 ? (int)(4 * b2) + 4 - f2 : (int)(4 * b1) + 4 - f1);
     if (has_key(k1, u) || has_key(k2, u)) return true;
-    if (k1.w == kEmpty || k2.w == kEmpty) return false;
+    if (free >= 0) return false;
     // both candidates full: the overflow scan from the first candidate
     uint32_t b = b1;
     for (;;) {
@@ -154,6 +157,19 @@ __device__ __forceinline__ void hash_insert(uint32_t* h, uint32_t cap, uint32_t 
         if (prev == kEmpty || prev == u) return;
         // another lane took the slot: read the candidates again
     }
+}
+
+// insert of a key whose lookup (nothing inserted since but by the other lanes
+// of this round) named a free slot: it, or the next ones of its bucket where
+// other lanes of the round came first; without a second look at the buckets
+__device__ __forceinline__ void hash_insert_at(uint32_t* h, uint32_t cap, uint32_t u, int free)
+{
+    if (free >= 0) {
+        do {
+            if (atomicCAS(&h[free], kEmpty, u) == kEmpty) return;
+        } while ((++free & 3) != 0);
+    }
+    hash_insert(h, cap, u);
 }
 
 __device__ __forceinline__ bool bitmap_test(const uint32_t* bm, uint32_t u)
@@ -498,7 +514,8 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
         // the end of the query (kept in vector registers: no scalar
         // registers and no ballot per count in the expansion loop)
         int st_exp = 0, st_ndist = 0, st_ins = 0, st_texp = 0;
-        int lc_edges = 0, lc_skip = 0, lc_ge1 = 0, lc_le0 = 0, lc_h = 0, lc_zero = 0, lc_pass = 0;
+        // (the other counts follow: a candidate is tested or gets a distance)
+        int lc_skip = 0, lc_ge1 = 0, lc_le0 = 0, lc_h = 0, st_zero = 0, st_pass = 0;
         int size = 0;
 
         if (qn > 0.f && qn < INFINITY) {
@@ -559,56 +576,37 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
             wave_sync();
 
             constexpr int NCW = (MAXL + 4) / 4;  // code dwords per edge (max)
+            const bool tests = a.mode == 0 || a.mode == 2;
+            // the node to expand, its distance, and the survivors of the
+            // last expansion that the list does not hold yet (km: their
+            // lanes; lane t: distance and id of survivor t)
+            uint32_t vid = v0;
+            float dv = wave_uniform(Sdist[0]);
+            uint64_t km = 0;
+            float dt = 0.f;
+            uint32_t ut = 0;
             for (;;) {
-                // pop: first unexpanded entry of the list
-                int pos = -1;
-                uint32_t vid;
-                float dv, delta;
-                const bool full = size >= efq;
-                if (REGL) {
-                    const uint64_t mk = ballot(lane < size && !(ri & kExpanded));
-                    if (!mk) break;
-                    pos = __ffsll((unsigned long long)mk) - 1;
-                    vid = (uint32_t)__builtin_amdgcn_readlane((int)ri, pos) & kIdMask;
-                    dv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), pos));
-                    delta = full ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), efq - 1))
-                                 : INFINITY;
-                    if (lane == pos) ri |= kExpanded;
-                } else {
-                    for (int c0 = lb; c0 < size; c0 += kWave) {
-                        const int p = c0 + lane;
-                        const uint64_t mk = ballot(p < size && !(Li[p] & kExpanded));
-                        if (mk) {
-                            pos = c0 + __ffsll((unsigned long long)mk) - 1;
-                            break;
-                        }
-                    }
-                    if (pos < 0) break;
-                    lb = pos + 1;
-                    vid = wave_uniform(Li[pos] & kIdMask);
-                    dv = Ld[pos];
-                    delta = full ? Ld[efq - 1] : INFINITY;
-                    wave_sync();
-                    if (lane == 0) Li[pos] = vid | kExpanded;
-                }
-                ++st_exp;
-                const bool testing = (a.mode == 0 || a.mode == 2) && full;
-                st_texp += testing ? 1 : 0;
-
-                // ids, codes and scalars depend on v only: one round trip.
-                // Every lane issues the same loads in straight-line code, the
-                // id first, so that the visited filter waits for the id alone
-                // while the record is in flight: lanes past R read edge R-1's
-                // again, and the record is read through a buffer resource
-                // whose range is the node's record, or empty when the
-                // expansion runs no test (out-of-range buffer loads return
-                // zero without touching memory).
+                const int nS = popc(km);
+                const bool full = size + nS >= efq;
+                const bool testing = tests && full;
+                // ids, codes and scalars depend on the node only: one round
+                // trip.  Every lane issues the same loads in straight-line
+                // code, the id first, so that the visited filter waits for
+                // the id alone while the record is in flight: lanes past R
+                // read edge R-1's again, and the record is read through a
+                // buffer resource whose range is the node's record, or empty
+                // when the expansion runs no test (out-of-range buffer loads
+                // return zero without touching memory).  The node is known
+                // from the distances alone, so the merge of the last
+                // survivors and the bookkeeping of the pop run while these
+                // loads are in flight.
                 const int le = lane < R ? lane : R - 1;
                 int32_t u = a.graph[(int64_t)vid * R + le];
                 const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                     const_cast<uint8_t*>(a.rec) + (int64_t)vid * a.node_stride, 0,
                     testing ? a.node_stride : 0, kBufferRsrcWord3);
                 float4 sc4;
+                uint2 sch;
                 uint32_t cw[NCW];
                 uint32_t csc = 0u;  // compact: the two scalar codes of the edge
                 if (CP) {
@@ -620,36 +618,212 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                     for (int i = 1; i < NCW; ++i) cw[i] = 0u;
                     csc = __builtin_amdgcn_raw_buffer_load_b16(rs, a.scal_off + 2 * le, 0, 0);
                 } else {
-                    if (H16) {
-                        // halves: g_e/|e|, 1/|e|, w_reg, sqrt(L) w_res
-                        const uint2 h = __builtin_bit_cast(
-                            uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, a.scal_off + 8 * le, 0, 0));
-                        sc4 = make_float4((float)__builtin_bit_cast(_Float16, (uint16_t)(h.x & 0xffffu)),
-                                          (float)__builtin_bit_cast(_Float16, (uint16_t)(h.x >> 16)),
-                                          (float)__builtin_bit_cast(_Float16, (uint16_t)(h.y & 0xffffu)),
-                                          (float)__builtin_bit_cast(_Float16, (uint16_t)(h.y >> 16)));
-                    } else {
+                    if (H16)
+                        sch = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, a.scal_off + 8 * le, 0, 0));
+                    else
                         sc4 = __builtin_bit_cast(
                             float4, __builtin_amdgcn_raw_buffer_load_b128(rs, a.scal_off + 16 * le, 0, 0));
-                    }
                     // the edge's codes, or in SimHash mode its two signature
                     // dwords (the dwords read past them, zero or another
                     // edge's bytes within the record, are cleared): one load
                     // shape for both modes
-                    const bool sim = a.mode == 2;
-                    const int cb = sim ? a.sig_off + 8 * le : a.codes_off + 4 * NCW * le;
+                    const int cb = a.mode == 2 ? a.sig_off + 8 * le : a.codes_off + 4 * NCW * le;
                     load_words<NCW>(rs, cb, cw);  // zero past the codes of L
+                }
+
+                // merge of the last expansion's survivors
+                if (nS != 0) {
+                    const bool keep = (km >> lane) & 1u;
+                    const uint64_t skey = keep ? sort_key(dt, ut) : ~0ull;
+                    if (REGL) {
+                        // list entry i (lane i) moves up by the number of
+                        // survivors below it; survivor t goes to (survivors below
+                        // it) + (list entries below it).  Positions from cap = ef
+                        // on are dropped (the launch guarantees cap = ef).
+                        const bool inl = lane < size;
+                        const uint64_t lk = inl ? sort_key(rd, ri) : ~0ull;
+                        int rS = 0, lo = 0, sh = 0;
+                        for (uint64_t mm = km; mm; mm &= mm - 1) {
+                            const int t = __ffsll((unsigned long long)mm) - 1;
+                            const uint64_t kt = readlane64(skey, t);
+                            rS += kt < skey;
+                            sh += kt < lk;
+                            const int nb = popc(ballot(lk < kt));  // (by all lanes)
+                            lo = lane == t ? nb : lo;
+                        }
+                        const int lpos = lane + sh;
+                        const int spos = lo + rS;
+                        wave_sync();  // Sdist / Su were read above
+                        if (inl && lpos < cap) {
+                            Sdist[lpos] = rd;
+                            Su[lpos] = ri;
+                        }
+                        if (keep && spos < cap) {
+                            Sdist[spos] = dt;
+                            Su[spos] = ut;
+                        }
+                        const int total = size + nS < cap ? size + nS : cap;
+                        wave_sync();
+                        rd = lane < total ? Sdist[lane] : INFINITY;
+                        ri = lane < total ? Su[lane] : 0u;
+                        size = total;
+                        wave_sync();
+                    } else {
+                        // merge in place.  Survivor t goes to lo + rS: the list
+                        // entries below it plus the survivors below it.  lo by
+                        // the last entries of 64 blocks of the list (one read),
+                        // then a search of one block by every survivor at once;
+                        // the entries from the first survivor's place on move up
+                        // by the number of survivors before them, from the back,
+                        // so that nothing is overwritten unread.  (Comparing every
+                        // entry with every survivor instead took 12 instructions
+                        // a survivor and chunk of 64, now 3 and only from the
+                        // first survivor's chunk on.)
+                        const int S = (size + kWave - 1) / kWave;  // entries per block
+                        int rS = 0, lo = 0;
+                        {
+                            const int q = (lane + 1) * S - 1;
+                            const uint64_t lk = q < size ? sort_key(Ld[q], Li[q]) : ~0ull;
+                            for (uint64_t mm = km; mm; mm &= mm - 1) {
+                                const int t = __ffsll((unsigned long long)mm) - 1;
+                                const uint64_t kt = readlane64(skey, t);
+                                rS += kt < skey;
+                                const int nb = popc(ballot(lk < kt));  // (by all lanes)
+                                lo = lane == t ? nb : lo;
+                            }
+                        }
+                        lo *= S;
+                        if (S > 1) {
+                            int hi = lo + S - 1 < size ? lo + S - 1 : size;
+                            for (int w = S; w > 1; w = (w + 1) >> 1) {
+                                const int mid = (lo + hi) >> 1;
+                                const bool open = keep && lo < hi;
+                                const bool below = open && sort_key(Ld[mid], Li[mid]) < skey;
+                                lo = below ? mid + 1 : lo;
+                                hi = open && !below ? mid : hi;
+                            }
+                        }
+                        int minpos = size;
+                        for (uint64_t mm = km; mm; mm &= mm - 1) {
+                            const int l = __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1);
+                            minpos = l < minpos ? l : minpos;
+                        }
+                        for (int c0 = (size - 1) & ~(kWave - 1); c0 + kWave > minpos && c0 >= 0; c0 -= kWave) {
+                            const int p = c0 + lane;
+                            const bool in = p < size && p >= minpos;
+                            const float dd = in ? Ld[p] : 0.f;
+                            const uint32_t id = in ? Li[p] : 0u;
+                            int to = p;
+                            for (uint64_t mm = km; mm; mm &= mm - 1)
+                                to += __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1) <= p;
+                            wave_sync();
+                            if (in && to < cap + slack) {
+                                Ld[to] = dd;
+                                Li[to] = id;
+                            }
+                            wave_sync();
+                        }
+                        const int mpos = lo + rS;
+                        if (keep && mpos < cap + slack) {
+                            Ld[mpos] = dt;
+                            Li[mpos] = ut;
+                        }
+                        wave_sync();
+                        // compaction, front to back: entries beyond ef leave once
+                        // expanded, and at most cap entries stay (nothing to do when
+                        // cap = ef: everything beyond is dropped)
+                        const int total = size + nS;
+                        int w = efq < total ? efq : total;
+                        if (cap > efq) {
+                            for (int c0 = w; c0 < total; c0 += kWave) {
+                                const int p = c0 + lane;
+                                const bool vld = p < total;
+                                const uint32_t id = vld ? Li[p] : 0u;
+                                const float dd = vld ? Ld[p] : 0.f;
+                                const bool kp = vld && !(id & kExpanded);
+                                const uint64_t kmask = ballot(kp);
+                                const int ix = w + lanes_before(kmask);
+                                wave_sync();
+                                if (kp && ix < cap + slack) {
+                                    Ld[ix] = dd;
+                                    Li[ix] = id;
+                                }
+                                wave_sync();
+                                w += popc(kmask);
+                            }
+                        } else {
+                            w = total;
+                        }
+                        if (w > cap && pool == 0) status |= kStatusPoolFull;
+                        size = w < cap ? w : cap;
+                        lb = lb < efq ? lb : efq;
+                        lb = lb < minpos ? lb : minpos;
+                        wave_sync();
+                    }
+                }
+                // the popped entry is marked, and the entry that comes next
+                // if no survivor of this expansion comes before it is found
+                uint32_t nid = 0u;
+                float nd = 0.f;
+                bool more;
+                float delta;
+                if (REGL) {
+                    if ((ri & kIdMask) == vid && lane < size) ri |= kExpanded;
+                    const uint64_t rest = ballot(lane < size && !(ri & kExpanded));
+                    more = rest != 0;
+                    const int p1 = more ? __ffsll((unsigned long long)rest) - 1 : 0;
+                    nid = (uint32_t)__builtin_amdgcn_readlane((int)ri, p1);
+                    nd = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), p1));
+                    delta = full ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), efq - 1))
+                                 : INFINITY;
+                } else {
+                    // vid is the first unexpanded entry from lb on, nid the
+                    // second
+                    int p1 = -1;
+                    bool seen = false;
+                    for (int c0 = lb; c0 < size; c0 += kWave) {
+                        const int p = c0 + lane;
+                        uint64_t mk = ballot(p < size && !(Li[p] & kExpanded));
+                        if (mk && !seen) {
+                            const int p0 = c0 + __ffsll((unsigned long long)mk) - 1;
+                            if (lane == 0) Li[p0] = vid | kExpanded;
+                            seen = true;
+                            mk &= mk - 1;
+                        }
+                        if (mk) {
+                            p1 = c0 + __ffsll((unsigned long long)mk) - 1;
+                            break;
+                        }
+                    }
+                    more = p1 >= 0;
+                    lb = more ? p1 : size;
+                    if (more) {
+                        nid = wave_uniform(Li[p1]);
+                        nd = wave_uniform(Ld[p1]);
+                    }
+                    delta = full ? Ld[efq - 1] : INFINITY;
+                    wave_sync();
+                }
+                ++st_exp;
+                st_texp += testing ? 1 : 0;
+                if (H16)
+                    // halves: g_e/|e|, 1/|e|, w_reg, sqrt(L) w_res
+                    sc4 = make_float4((float)__builtin_bit_cast(_Float16, (uint16_t)(sch.x & 0xffffu)),
+                                      (float)__builtin_bit_cast(_Float16, (uint16_t)(sch.x >> 16)),
+                                      (float)__builtin_bit_cast(_Float16, (uint16_t)(sch.y & 0xffffu)),
+                                      (float)__builtin_bit_cast(_Float16, (uint16_t)(sch.y >> 16)));
+                if (!CP) {
 #pragma unroll
-                    for (int i = 2; i < NCW; ++i) cw[i] = sim ? 0u : cw[i];
+                    for (int i = 2; i < NCW; ++i) cw[i] = a.mode == 2 ? 0u : cw[i];
                 }
                 if (lane >= R) u = -1;
                 const float sg = sc4.x, se = sc4.y, sw = sc4.z, sr = sc4.w;
                 const bool valid = u >= 0;
-                lc_edges += valid ? 1 : 0;
                 bool vis = false;
+                int hfree = -1;
                 if (valid)
                     vis = spilled ? bitmap_test(bitmap, (uint32_t)u)
-                                  : hash_lookup(hash, (uint32_t)hcap, (uint32_t)u);
+                                  : hash_lookup(hash, (uint32_t)hcap, (uint32_t)u, hfree);
                 lc_skip += vis ? 1 : 0;
                 const bool cand = valid && !vis;
                 bool pass = cand;
@@ -731,15 +905,21 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                         pass = zero ? num < 0.f : (ge1 ? false : (le0 ? true : hpass));
                     }
                     // every tested edge gets exactly one kind
-                    lc_zero += kind == 0 ? 1 : 0;
+                    st_zero += popc(ballot(kind == 0));
                     lc_ge1 += kind == 1 ? 1 : 0;
                     lc_le0 += kind == 2 ? 1 : 0;
                     lc_h += kind == 3 ? 1 : 0;
-                    lc_pass += (cand && pass) ? 1 : 0;
                 }
                 const uint64_t smask = ballot(pass);
                 const int ns = popc(smask);
-                if (ns == 0) continue;
+                st_pass += testing ? ns : 0;
+                km = 0;
+                if (ns == 0) {
+                    if (!more) break;
+                    vid = nid;
+                    dv = nd;
+                    continue;
+                }
 
                 // visited := visited + survivors
                 if (!spilled && nvis + ns > a.visit_limit) {
@@ -759,12 +939,12 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                     status |= kStatusSpill;
                 }
                 if (pass) {
-                    const int t = popc(smask & lanemask_lt());
+                    const int t = lanes_before(smask);
                     if (spilled) {
                         atomicOr(bitmap + ((uint32_t)u >> 5), 1u << ((uint32_t)u & 31u));
                         if (nlist + t < a.spill_list_cap) slist[nlist + t] = (uint32_t)u;
                     } else {
-                        hash_insert(hash, (uint32_t)hcap, (uint32_t)u);
+                        hash_insert_at(hash, (uint32_t)hcap, (uint32_t)u, hfree);
                     }
                     Su[t] = (uint32_t)u;
                 }
@@ -777,136 +957,39 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 wave_sync();
 
                 // survivors that enter the list stay in their own lanes
-                // (lane t = survivor t) with their sort keys in registers
+                // (lane t = survivor t); the next node is the closest of
+                // them or the list's next
                 bool keep = false;
-                float dt = 0.f;
-                uint32_t ut = 0;
-                uint64_t skey = ~0ull;
                 if (lane < ns) {
                     dt = Sdist[lane];
                     ut = Su[lane];
                     keep = !full || dt < delta;
-                    if (keep) skey = sort_key(dt, ut);
-                }
-                const uint64_t km = ballot(keep);
-                const int nS = popc(km);
-                st_ins += nS;
-                if (nS == 0) continue;
-
-                if (REGL) {
-                    // list entry i (lane i) moves up by the number of
-                    // survivors below it; survivor t goes to (survivors below
-                    // it) + (list entries below it).  Positions from cap = ef
-                    // on are dropped (the launch guarantees cap = ef).
-                    const bool inl = lane < size;
-                    const uint64_t lk = inl ? sort_key(rd, ri) : ~0ull;
-                    int rS = 0, lo = 0, sh = 0;
-                    for (uint64_t mm = km; mm; mm &= mm - 1) {
-                        const int t = __ffsll((unsigned long long)mm) - 1;
-                        const uint64_t kt = readlane64(skey, t);
-                        rS += kt < skey;
-                        const bool below = inl && lk < kt;
-                        sh += (inl && !below) ? 1 : 0;
-                        const int nb = popc(ballot(below));
-                        lo += (lane == t) ? nb : 0;
-                    }
-                    const int lpos = lane + sh;
-                    const int spos = lo + rS;
-                    wave_sync();  // Sdist / Su were read above
-                    if (inl && lpos < cap) {
-                        Sdist[lpos] = rd;
-                        Su[lpos] = ri;
-                    }
-                    if (keep && spos < cap) {
-                        Sdist[spos] = dt;
-                        Su[spos] = ut;
-                    }
-                    const int total = size + nS < cap ? size + nS : cap;
-                    wave_sync();
-                    rd = lane < total ? Sdist[lane] : INFINITY;
-                    ri = lane < total ? Su[lane] : 0u;
-                    size = total;
-                    wave_sync();
-                    continue;
-                }
-
-                // merge in place: rank of each survivor among the survivors,
-                // number of list entries below it (lo), and for each list
-                // entry the number of survivors below it (its shift).  Keys
-                // are broadcast from the survivor lanes; chunks of the list
-                // move from the back so nothing is overwritten unread.
-                int rS = 0;
-                for (uint64_t mm = km; mm; mm &= mm - 1) {
-                    const int t = __ffsll((unsigned long long)mm) - 1;
-                    const uint64_t kt = readlane64(skey, t);
-                    rS += kt < skey;
-                }
-                int lo = 0;
-                for (int c0 = ((size - 1) / kWave) * kWave; c0 >= 0; c0 -= kWave) {
-                    const int p = c0 + lane;
-                    const bool in = p < size;
-                    const float dd = in ? Ld[p] : 0.f;
-                    const uint32_t id = in ? Li[p] : 0u;
-                    const uint64_t lk = in ? sort_key(dd, id) : ~0ull;
-                    int sh = 0;
-                    for (uint64_t mm = km; mm; mm &= mm - 1) {
-                        const int t = __ffsll((unsigned long long)mm) - 1;
-                        const uint64_t kt = readlane64(skey, t);
-                        const bool below = lk < kt;
-                        const int nb = popc(ballot(below));
-                        lo += (lane == t) ? nb : 0;
-                        sh += (in && !below) ? 1 : 0;
-                    }
-                    wave_sync();
-                    if (in && sh && p + sh < cap + slack) {
-                        Ld[p + sh] = dd;
-                        Li[p + sh] = id;
-                    }
-                    wave_sync();
-                }
-                const int mpos = keep ? lo + rS : 0x7fffffff;
-                if (keep && mpos < cap + slack) {
-                    Ld[mpos] = dt;
-                    Li[mpos] = ut;
-                }
-                int minpos = mpos;
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    const int other = __shfl_xor(minpos, o, kWave);
-                    minpos = other < minpos ? other : minpos;
                 }
                 wave_sync();
-                // compaction, front to back: entries beyond ef leave once
-                // expanded, and at most cap entries stay (nothing to do when
-                // cap = ef: everything beyond is dropped)
-                const int total = size + nS;
-                int w = efq < total ? efq : total;
-                if (cap > efq) {
-                    for (int c0 = w; c0 < total; c0 += kWave) {
-                        const int p = c0 + lane;
-                        const bool vld = p < total;
-                        const uint32_t id = vld ? Li[p] : 0u;
-                        const float dd = vld ? Ld[p] : 0.f;
-                        const bool kp = vld && !(id & kExpanded);
-                        const uint64_t kmask = ballot(kp);
-                        const int ix = w + popc(kmask & lanemask_lt());
-                        wave_sync();
-                        if (kp && ix < cap + slack) {
-                            Ld[ix] = dd;
-                            Li[ix] = id;
-                        }
-                        wave_sync();
-                        w += popc(kmask);
+                km = ballot(keep);
+                st_ins += popc(km);
+                if (km != 0) {
+                    const uint32_t ob = keep ? order_bits(dt) : 0xFFFFFFFFu;
+                    const uint32_t om = wave_min(ob);
+                    uint64_t tie = ballot(keep && ob == om);
+                    int t = __ffsll((unsigned long long)tie) - 1;
+                    uint32_t tid = (uint32_t)__builtin_amdgcn_readlane((int)ut, t);
+                    const float td = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dt), t));
+                    for (tie &= tie - 1; tie; tie &= tie - 1) {  // equal distances: the smaller id
+                        t = __ffsll((unsigned long long)tie) - 1;
+                        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)ut, t);
+                        tid = o < tid ? o : tid;
                     }
-                } else {
-                    w = total;
+                    const uint32_t on = order_bits(nd);
+                    if (!more || om < on || (om == on && tid < nid)) {
+                        nid = tid;
+                        nd = td;
+                        more = true;
+                    }
                 }
-                if (w > cap && pool == 0) status |= kStatusPoolFull;
-                size = w < cap ? w : cap;
-                minpos = wave_uniform(minpos);
-                lb = lb < efq ? lb : efq;
-                lb = lb < minpos ? lb : minpos;
-                wave_sync();
+                if (!more) break;
+                vid = nid;
+                dv = nd;
             }
             if (spilled && nlist <= a.spill_list_cap) {
                 // clear the words this query set: the ids the hash held at
@@ -971,16 +1054,16 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 ca.dists[qi * kstride + t] = ok ? Ld[t] : INFINITY;
             }
         }
-        const int st_edges = wave_sum_int(lc_edges), st_skip = wave_sum_int(lc_skip);
-        const int st_ge1 = wave_sum_int(lc_ge1), st_le0 = wave_sum_int(lc_le0);
-        const int st_h = wave_sum_int(lc_h), st_zero = wave_sum_int(lc_zero);
-        const int st_pass = wave_sum_int(lc_pass);
+        const int st_skip = wave_sum_int(lc_skip), st_ge1 = wave_sum_int(lc_ge1);
+        const int st_le0 = wave_sum_int(lc_le0), st_h = wave_sum_int(lc_h);
+        const int st_tests = st_zero + st_ge1 + st_le0 + st_h;
         if (ca.stats && lane == 0) {
             int32_t* o = ca.stats + qi * kNumStats;
             o[0] = st_exp;
-            o[1] = st_edges;
+            // visited ones, tested ones, and those that got a distance untested
+            o[1] = st_skip + st_tests + (st_ndist > 0 ? st_ndist - 1 : 0) - st_pass;
             o[2] = st_skip;
-            o[3] = st_zero + st_ge1 + st_le0 + st_h;
+            o[3] = st_tests;
             o[4] = st_ge1;
             o[5] = st_le0;
             o[6] = st_h;
@@ -1046,7 +1129,7 @@ __global__ __launch_bounds__(1024) void k_classify(const int32_t* kq, const int3
         int rank = 0;
         for (int cc = 0; cc < nclass; ++cc) {
             const uint64_t mk = ballot(c == cc);
-            if (c == cc) rank = popc(mk & lanemask_lt());
+            if (c == cc) rank = lanes_before(mk);
             if (lane == 0) wc[wv][cc] = (uint32_t)popc(mk);
         }
         __syncthreads();

@@ -39,11 +39,10 @@ __device__ __forceinline__ void wave_mem_order()
     __builtin_amdgcn_wave_barrier();
 }
 
-// lanes below this one
-__device__ __forceinline__ uint64_t lanemask_lt()
+// number of lanes of the mask below this one (no lane mask kept in registers)
+__device__ __forceinline__ int lanes_before(uint64_t mask)
 {
-    const int l = lane_id();
-    return l == 0 ? 0ull : (~0ull >> (64 - l));
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 __device__ __forceinline__ int popc(uint64_t x) { return __popcll(x); }
@@ -96,6 +95,20 @@ __device__ __forceinline__ int wave_sum_int(int v)
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;
+}
+
+// smallest value of the wave, as a scalar: four steps within rows of 16 lanes
+// and two across them, each a DPP move and a minimum (no LDS round trip)
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+    auto step = [&](uint32_t o) { v = o < v ? o : v; };
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xF, 0xF, false));  // row_bcast:15
+    step((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xF, 0xF, false));  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // sum within aligned groups of G lanes (G a power of two <= 64)
