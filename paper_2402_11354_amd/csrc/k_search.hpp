@@ -21,6 +21,8 @@
 //   all, while R is not full) are merged into the list.
 #pragma once
 
+#include <type_traits>
+
 #include "peos_device.hpp"
 
 namespace peos {
@@ -74,6 +76,17 @@ constexpr int kStatusZeroQuery = 1;
 constexpr int kStatusPoolFull = 2;
 constexpr int kStatusSpill = 4;
 
+// An entry of the candidate list: the distance as an unsigned number that
+// sorts like it, then the id, then the "expanded" bit, so that entries of
+// different nodes compare as (distance, id) whatever their bits.  A place
+// without an entry holds all ones: above every entry, and expanded.
+constexpr uint64_t kNoEntry = ~0ull;
+
+__device__ __forceinline__ uint64_t list_entry(uint32_t bits, uint32_t id)
+{
+    return (static_cast<uint64_t>(bits) << 32) | (id << 1);
+}
+
 // visited set: buckets of four slots (one 16-byte LDS read each) over
 // cap/4 buckets, two candidate buckets per key (two multiplicative hashes
 // scaled to [0, cap/4)).  An insert takes the candidate with more free
@@ -101,28 +114,33 @@ __device__ __forceinline__ int free_slots(uint4 k)
 
 __device__ __forceinline__ bool has_key(uint4 k, uint32_t u)
 {
-    return k.x == u || k.y == u || k.z == u || k.w == u;
+    return (k.x == u) | (k.y == u) | (k.z == u) | (k.w == u);
 }
 
-// free: the slot an insert of u would take by these reads (-1: both full)
-__device__ __forceinline__ bool hash_lookup(const uint32_t* h, uint32_t cap, uint32_t u, int& free)
+// free: the slot an insert of u would take by these reads (-1: both full).
+// Straight-line code for every lane (valid: the lane has a key); only a lane
+// whose candidates are both full scans on.
+__device__ __forceinline__ bool hash_lookup(const uint32_t* h, uint32_t cap, uint32_t u, bool valid, int& free)
 {
     const uint32_t nb = cap >> 2;
     const uint32_t b1 = hash_bucket(u, nb), b2 = hash_bucket2(u, nb);
     const uint4 k1 = reinterpret_cast<const uint4*>(h)[b1];
     const uint4 k2 = reinterpret_cast<const uint4*>(h)[b2];
     const int f1 = free_slots(k1), f2 = free_slots(k2);
-    free = (f1 | f2) == 0 ? -1 : (f2 > f1 ? (int)(4 * b2) + 4 - f2 : (int)(4 * b1) + 4 - f1);
-    if (has_key(k1, u) || has_key(k2, u)) return true;
-    if (free >= 0) return false;
-    // both candidates full: the overflow scan from the first candidate
-    uint32_t b = b1;
-    for (;;) {
-        b = (b + 1u == nb) ? 0u : b + 1u;
-        const uint4 k = reinterpret_cast<const uint4*>(h)[b];
-        if (has_key(k, u)) return true;
-        if (k.w == kEmpty) return false;
+    const bool second = f2 > f1;
+    free = (f1 | f2) == 0 ? -1 : (int)(4 * (second ? b2 : b1)) + 4 - (second ? f2 : f1);
+    bool found = has_key(k1, u) | has_key(k2, u);
+    if (valid && !found && free < 0) {
+        // both candidates full: the overflow scan from the first candidate
+        uint32_t b = b1;
+        for (;;) {
+            b = (b + 1u == nb) ? 0u : b + 1u;
+            const uint4 k = reinterpret_cast<const uint4*>(h)[b];
+            found = has_key(k, u);
+            if (found || k.w == kEmpty) break;
+        }
     }
+    return valid && found;
 }
 
 __device__ __forceinline__ void hash_insert(uint32_t* h, uint32_t cap, uint32_t u)
@@ -172,10 +190,10 @@ __device__ __forceinline__ void hash_insert_at(uint32_t* h, uint32_t cap, uint32
     hash_insert(h, cap, u);
 }
 
-__device__ __forceinline__ bool bitmap_test(const uint32_t* bm, uint32_t u)
+// the word of the bitmap that holds u's bit
+__device__ __forceinline__ uint32_t bitmap_word(const uint32_t* bm, uint32_t u)
 {
-    const uint32_t w = __hip_atomic_load(bm + (u >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return (w >> (u & 31u)) & 1u;
+    return __hip_atomic_load(bm + (u >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Exact distances of ns vectors (ids in Su) to the query, G lanes per vector
@@ -463,10 +481,9 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
     // the list in LDS (none when it lives in registers: the output then
     // stages it in the visited hash, which is dead by then)
     const int lds_list = REGL ? 0 : listcap + slack;
-    float* Lr = tab + 2 * m * TW;
-    uint32_t* hash = reinterpret_cast<uint32_t*>(Lr) + 2 * lds_list;
-    float* Ld = REGL ? reinterpret_cast<float*>(hash) : Lr;
-    uint32_t* Li = REGL ? hash + kWave : reinterpret_cast<uint32_t*>(Lr) + lds_list;
+    uint64_t* Lr = reinterpret_cast<uint64_t*>(tab + 2 * m * TW);
+    uint32_t* hash = reinterpret_cast<uint32_t*>(Lr + lds_list);
+    uint64_t* Le = REGL ? reinterpret_cast<uint64_t*>(hash) : Lr;
     uint32_t* bitmap = a.spill + (int64_t)blockIdx.x * a.spill_words;
     // The bitmap is cleared whole when this workgroup first spills; after
     // that a spilled query lists the ids it sets past the hash's and clears
@@ -555,36 +572,31 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 hash_insert(hash, (uint32_t)hcap, v0);
             }
             wave_sync();
-            // list entry `lane` (REGL)
-            float rd = INFINITY;
-            uint32_t ri = 0u;
-            if (REGL) {
-                if (lane == 0) {
-                    rd = Sdist[0];
-                    ri = v0;
-                }
-            } else if (lane == 0) {
-                Ld[0] = Sdist[0];
-                Li[0] = v0;
-            }
+            const uint64_t first = list_entry(order_bits(Sdist[0]), v0);
+            uint64_t re = lane == 0 ? first : kNoEntry;  // list entry `lane` (REGL)
+            if (!REGL && lane == 0) Le[0] = first;
             size = 1;
             int nvis = 1;
             bool spilled = false;
             int nlist = 0;  // ids set in the bitmap after the spill
             st_ndist = 1;
-            int lb = 0;  // every entry before lb is expanded
+            int lb = 0;         // every entry before lb is expanded (list in LDS)
+            bool late = false;  // an entry past the first ef has been expanded since the last compaction
             wave_sync();
 
             constexpr int NCW = (MAXL + 4) / 4;  // code dwords per edge (max)
             const bool tests = a.mode == 0 || a.mode == 2;
             // the node to expand, its distance, and the survivors of the
             // last expansion that the list does not hold yet (km: their
-            // lanes; lane t: distance and id of survivor t)
+            // lanes; surv: lane t's, as a list entry)
             uint32_t vid = v0;
             float dv = wave_uniform(Sdist[0]);
             uint64_t km = 0;
-            float dt = 0.f;
-            uint32_t ut = 0;
+            uint64_t surv = kNoEntry;
+            // its survivors that the visited set does not hold yet: their
+            // edges' lanes, and the free slots their lookups saw
+            uint64_t smask = 0;
+            int hfree = -1;
             for (;;) {
                 const int nS = popc(km);
                 const bool full = size + nS >= efq;
@@ -631,177 +643,201 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                     load_words<NCW>(rs, cb, cw);  // zero past the codes of L
                 }
 
+                // visited := visited + the last expansion's survivors (while
+                // the loads above are in flight)
+                if (smask != 0) {
+                    const int ns = popc(smask);
+                    const bool pass = (smask >> lane) & 1u;
+                    const int t = lanes_before(smask);
+                    const uint32_t us = Su[t];
+                    if (!spilled && nvis + ns > a.visit_limit) {
+                        if (bm_unknown) {
+                            for (int w = lane; w < (a.spill_bitmap_words >> 2); w += kWave)
+                                reinterpret_cast<uint4*>(bitmap)[w] = make_uint4(0u, 0u, 0u, 0u);
+                            wave_mem_order();
+                        }
+                        for (int w = lane; w < hcap; w += kWave) {
+                            const uint32_t k = hash[w];
+                            if (k != kEmpty) atomicOr(bitmap + (k >> 5), 1u << (k & 31u));
+                        }
+                        wave_mem_order();
+                        spilled = true;
+                        bm_unknown = true;
+                        nlist = 0;
+                        status |= kStatusSpill;
+                    }
+                    if (pass) {
+                        if (spilled) {
+                            atomicOr(bitmap + (us >> 5), 1u << (us & 31u));
+                            if (nlist + t < a.spill_list_cap) slist[nlist + t] = us;
+                        } else {
+                            hash_insert_at(hash, (uint32_t)hcap, us, hfree);
+                        }
+                    }
+                    if (spilled) nlist += ns;
+                    nvis += ns;
+                    wave_sync();
+                }
+
                 // merge of the last expansion's survivors
                 if (nS != 0) {
-                    const bool keep = (km >> lane) & 1u;
-                    const uint64_t skey = keep ? sort_key(dt, ut) : ~0ull;
                     if (REGL) {
                         // list entry i (lane i) moves up by the number of
-                        // survivors below it; survivor t goes to (survivors below
-                        // it) + (list entries below it).  Positions from cap = ef
-                        // on are dropped (the launch guarantees cap = ef).
-                        const bool inl = lane < size;
-                        const uint64_t lk = inl ? sort_key(rd, ri) : ~0ull;
+                        // survivors below it; survivor t goes to (survivors
+                        // below it) + (list entries below it).  Positions
+                        // from cap = ef on are dropped (the launch guarantees
+                        // cap = ef).
                         int rS = 0, lo = 0, sh = 0;
                         for (uint64_t mm = km; mm; mm &= mm - 1) {
                             const int t = __ffsll((unsigned long long)mm) - 1;
-                            const uint64_t kt = readlane64(skey, t);
-                            rS += kt < skey;
-                            sh += kt < lk;
-                            const int nb = popc(ballot(lk < kt));  // (by all lanes)
+                            const uint64_t kt = readlane64(surv, t);
+                            const bool above = kt < re;  // (of every lane: absent entries are above)
+                            const int nb = kWave - popc(ballot(above));
+                            rS += kt < surv;
+                            sh += above;
                             lo = lane == t ? nb : lo;
                         }
-                        const int lpos = lane + sh;
-                        const int spos = lo + rS;
-                        wave_sync();  // Sdist / Su were read above
-                        if (inl && lpos < cap) {
-                            Sdist[lpos] = rd;
-                            Su[lpos] = ri;
-                        }
-                        if (keep && spos < cap) {
-                            Sdist[spos] = dt;
-                            Su[spos] = ut;
-                        }
-                        const int total = size + nS < cap ? size + nS : cap;
+                        const int lpos = lane + sh, spos = lo + rS;
+                        uint64_t* St = reinterpret_cast<uint64_t*>(Su);  // Su and Sdist, read above
                         wave_sync();
-                        rd = lane < total ? Sdist[lane] : INFINITY;
-                        ri = lane < total ? Su[lane] : 0u;
-                        size = total;
+                        if (lpos < kWave) St[lpos] = re;
+                        if (((km >> lane) & 1u) && spos < kWave) St[spos] = surv;
+                        size = size + nS < cap ? size + nS : cap;
+                        wave_sync();
+                        const uint64_t e = St[lane];
+                        re = lane < size ? e : kNoEntry;
                         wave_sync();
                     } else {
-                        // merge in place.  Survivor t goes to lo + rS: the list
-                        // entries below it plus the survivors below it.  lo by
-                        // the last entries of 64 blocks of the list (one read),
-                        // then a search of one block by every survivor at once;
-                        // the entries from the first survivor's place on move up
-                        // by the number of survivors before them, from the back,
-                        // so that nothing is overwritten unread.  (Comparing every
-                        // entry with every survivor instead took 12 instructions
-                        // a survivor and chunk of 64, now 3 and only from the
-                        // first survivor's chunk on.)
-                        const int S = (size + kWave - 1) / kWave;  // entries per block
+                        // the same in place, 256 entries at a time from the
+                        // back, in registers between one round of reads and
+                        // one of writes; blocks wholly below every survivor
+                        // stay as they are
                         int rS = 0, lo = 0;
-                        {
-                            const int q = (lane + 1) * S - 1;
-                            const uint64_t lk = q < size ? sort_key(Ld[q], Li[q]) : ~0ull;
+                        bool drop = false;  // an expanded entry left the first ef
+                        auto merge_block = [&](auto count, int b0, bool first) {
+                            constexpr int N = decltype(count)::value;
+                            uint64_t e[N];
+                            int sh[N];
+#pragma unroll
+                            for (int c = 0; c < N; ++c) {
+                                const int p = b0 + c * kWave + lane;
+                                e[c] = p < size ? Le[p] : kNoEntry;
+                                sh[c] = 0;
+                            }
+                            int least = N * kWave;
                             for (uint64_t mm = km; mm; mm &= mm - 1) {
                                 const int t = __ffsll((unsigned long long)mm) - 1;
-                                const uint64_t kt = readlane64(skey, t);
-                                rS += kt < skey;
-                                const int nb = popc(ballot(lk < kt));  // (by all lanes)
-                                lo = lane == t ? nb : lo;
-                            }
-                        }
-                        lo *= S;
-                        if (S > 1) {
-                            int hi = lo + S - 1 < size ? lo + S - 1 : size;
-                            for (int w = S; w > 1; w = (w + 1) >> 1) {
-                                const int mid = (lo + hi) >> 1;
-                                const bool open = keep && lo < hi;
-                                const bool below = open && sort_key(Ld[mid], Li[mid]) < skey;
-                                lo = below ? mid + 1 : lo;
-                                hi = open && !below ? mid : hi;
-                            }
-                        }
-                        int minpos = size;
-                        for (uint64_t mm = km; mm; mm &= mm - 1) {
-                            const int l = __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1);
-                            minpos = l < minpos ? l : minpos;
-                        }
-                        for (int c0 = (size - 1) & ~(kWave - 1); c0 + kWave > minpos && c0 >= 0; c0 -= kWave) {
-                            const int p = c0 + lane;
-                            const bool in = p < size && p >= minpos;
-                            const float dd = in ? Ld[p] : 0.f;
-                            const uint32_t id = in ? Li[p] : 0u;
-                            int to = p;
-                            for (uint64_t mm = km; mm; mm &= mm - 1)
-                                to += __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1) <= p;
-                            wave_sync();
-                            if (in && to < cap + slack) {
-                                Ld[to] = dd;
-                                Li[to] = id;
+                                const uint64_t kt = readlane64(surv, t);
+                                int nb = N * kWave;
+#pragma unroll
+                                for (int c = 0; c < N; ++c) {
+                                    const bool above = kt < e[c];
+                                    nb -= popc(ballot(above));
+                                    sh[c] += above;
+                                }
+                                if (first) rS += kt < surv;
+                                lo = lane == t ? lo + nb : lo;
+                                least = nb < least ? nb : least;
                             }
                             wave_sync();
+#pragma unroll
+                            for (int c = 0; c < N; ++c) {
+                                const int p = b0 + c * kWave + lane;
+                                const bool in = p < size && sh[c] != 0;
+                                drop |= in && p < efq && p + sh[c] >= efq && (e[c] & 1u);
+                                if (in && p + sh[c] < cap + slack) Le[p + sh[c]] = e[c];
+                            }
+                            wave_sync();
+                            return least;
+                        };
+                        int b0 = (size - 1) & ~(4 * kWave - 1);
+                        int least;
+                        if (size - b0 <= kWave) least = merge_block(std::integral_constant<int, 1>(), b0, true);
+                        else if (size - b0 <= 2 * kWave) least = merge_block(std::integral_constant<int, 2>(), b0, true);
+                        else least = merge_block(std::integral_constant<int, 4>(), b0, true);
+                        while (b0 > 0 && least == 0) {
+                            b0 -= 4 * kWave;
+                            least = merge_block(std::integral_constant<int, 4>(), b0, false);
                         }
+                        lo += b0;
                         const int mpos = lo + rS;
-                        if (keep && mpos < cap + slack) {
-                            Ld[mpos] = dt;
-                            Li[mpos] = ut;
-                        }
+                        if (((km >> lane) & 1u) && mpos < cap + slack) Le[mpos] = surv;
                         wave_sync();
-                        // compaction, front to back: entries beyond ef leave once
-                        // expanded, and at most cap entries stay (nothing to do when
-                        // cap = ef: everything beyond is dropped)
+                        // compaction, front to back: entries beyond ef leave
+                        // once expanded, and at most cap entries stay (nothing
+                        // to do when cap = ef, everything beyond is dropped,
+                        // or when no expanded entry lies there)
                         const int total = size + nS;
-                        int w = efq < total ? efq : total;
-                        if (cap > efq) {
+                        int w = total;
+                        if (cap > efq && (late || ballot(drop) != 0)) {
+                            w = efq < total ? efq : total;
                             for (int c0 = w; c0 < total; c0 += kWave) {
                                 const int p = c0 + lane;
-                                const bool vld = p < total;
-                                const uint32_t id = vld ? Li[p] : 0u;
-                                const float dd = vld ? Ld[p] : 0.f;
-                                const bool kp = vld && !(id & kExpanded);
+                                const uint64_t e = p < total ? Le[p] : kNoEntry;
+                                const bool kp = !(e & 1u);
                                 const uint64_t kmask = ballot(kp);
                                 const int ix = w + lanes_before(kmask);
                                 wave_sync();
-                                if (kp && ix < cap + slack) {
-                                    Ld[ix] = dd;
-                                    Li[ix] = id;
-                                }
+                                if (kp && ix < cap + slack) Le[ix] = e;
                                 wave_sync();
                                 w += popc(kmask);
                             }
-                        } else {
-                            w = total;
+                            late = false;
+                            lb = lb < efq ? lb : efq;
                         }
                         if (w > cap && pool == 0) status |= kStatusPoolFull;
                         size = w < cap ? w : cap;
-                        lb = lb < efq ? lb : efq;
-                        lb = lb < minpos ? lb : minpos;
-                        wave_sync();
+                        // the first survivor's place
+                        for (uint64_t mm = km; mm; mm &= mm - 1) {
+                            const int l = __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1);
+                            lb = l < lb ? l : lb;
+                        }
                     }
                 }
                 // the popped entry is marked, and the entry that comes next
                 // if no survivor of this expansion comes before it is found
-                uint32_t nid = 0u;
-                float nd = 0.f;
+                uint32_t nid = 0u, nk = 0u;
                 bool more;
-                float delta;
+                float delta = INFINITY;
                 if (REGL) {
-                    if ((ri & kIdMask) == vid && lane < size) ri |= kExpanded;
-                    const uint64_t rest = ballot(lane < size && !(ri & kExpanded));
+                    re |= (uint32_t)((uint32_t)re == 2u * vid);
+                    const uint64_t rest = ballot(!(re & 1u));  // (absent entries count as expanded)
                     more = rest != 0;
-                    const int p1 = more ? __ffsll((unsigned long long)rest) - 1 : 0;
-                    nid = (uint32_t)__builtin_amdgcn_readlane((int)ri, p1);
-                    nd = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), p1));
-                    delta = full ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rd), efq - 1))
-                                 : INFINITY;
+                    const uint64_t e = readlane64(re, more ? __ffsll((unsigned long long)rest) - 1 : 0);
+                    nid = (uint32_t)e >> 1;
+                    nk = (uint32_t)(e >> 32);
+                    if (full) delta = bits_value((uint32_t)(readlane64(re, efq - 1) >> 32));
                 } else {
+                    uint32_t dk = 0u;
+                    if (full) dk = (uint32_t)(Le[efq - 1] >> 32);
                     // vid is the first unexpanded entry from lb on, nid the
                     // second
-                    int p1 = -1;
+                    more = false;
                     bool seen = false;
-                    for (int c0 = lb; c0 < size; c0 += kWave) {
+                    int c0 = lb;
+                    lb = size;
+                    for (; c0 < size; c0 += kWave) {
                         const int p = c0 + lane;
-                        uint64_t mk = ballot(p < size && !(Li[p] & kExpanded));
+                        const uint64_t e = p < size ? Le[p] : kNoEntry;
+                        uint64_t mk = ballot(!(e & 1u));
                         if (mk && !seen) {
-                            const int p0 = c0 + __ffsll((unsigned long long)mk) - 1;
-                            if (lane == 0) Li[p0] = vid | kExpanded;
+                            const int t = __ffsll((unsigned long long)mk) - 1;
+                            if (lane == t) Le[p] = e | 1u;
+                            late |= c0 + t >= efq;
                             seen = true;
                             mk &= mk - 1;
                         }
                         if (mk) {
-                            p1 = c0 + __ffsll((unsigned long long)mk) - 1;
+                            const int t = __ffsll((unsigned long long)mk) - 1;
+                            const uint64_t n = readlane64(e, t);
+                            nid = (uint32_t)n >> 1;
+                            nk = (uint32_t)(n >> 32);
+                            lb = c0 + t;
+                            more = true;
                             break;
                         }
                     }
-                    more = p1 >= 0;
-                    lb = more ? p1 : size;
-                    if (more) {
-                        nid = wave_uniform(Li[p1]);
-                        nd = wave_uniform(Ld[p1]);
-                    }
-                    delta = full ? Ld[efq - 1] : INFINITY;
+                    if (full) delta = bits_value(wave_uniform(dk));
                     wave_sync();
                 }
                 ++st_exp;
@@ -819,47 +855,37 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 if (lane >= R) u = -1;
                 const float sg = sc4.x, se = sc4.y, sw = sc4.z, sr = sc4.w;
                 const bool valid = u >= 0;
+                // the visited filter's reads go out before the test, which
+                // every lane computes (a lane without a candidate discards
+                // it), so that neither waits for the other
                 bool vis = false;
-                int hfree = -1;
-                if (valid)
-                    vis = spilled ? bitmap_test(bitmap, (uint32_t)u)
-                                  : hash_lookup(hash, (uint32_t)hcap, (uint32_t)u, hfree);
-                lc_skip += vis ? 1 : 0;
-                const bool cand = valid && !vis;
-                bool pass = cand;
+                uint32_t vw = 0u;
+                if (spilled) vw = bitmap_word(bitmap, (uint32_t)(valid ? u : 0));
+                else vis = hash_lookup(hash, (uint32_t)hcap, (uint32_t)u, valid, hfree);
+                bool pass = true;
+                int kind = -1;
                 if (testing) {
-                    int kind = -1;
-                    if (cand && CP) {
+                    if (CP) {
                         // compact records: w_reg = 1, w_res = 0, decoded
                         // scalars (A_r a lower bound of the exact one), the
                         // quantile from the table (its bin's smallest T)
                         const float diff = (a.metric == 0) ? 0.5f * (dv - delta) : (dv - delta);
                         const uint32_t ci = csc >> 8;
-                        if (ci == 255u) {
-                            kind = 0;
-                            pass = diff < 0.f;
-                        } else {
-                            const float gp = (a.metric == 0) ? fmaf((float)(csc & 0xFFu), sc4.y, sc4.x) : 0.f;
-                            const float ie = fmaf((float)ci + (diff < 0.f ? 0.5f : -0.5f), sc4.w, sc4.z);
-                            const float A = (a.metric != 1) ? fmaf(diff, ie, gp) * inv_qn : diff * ie;
-                            if (A >= 1.f) {
-                                kind = 1;
-                                pass = false;
-                            } else if (A <= 0.f) {
-                                kind = 2;
-                                pass = true;
-                            } else {
-                                kind = 3;
-                                float h = 0.f;
+                        const float gp = (a.metric == 0) ? fmaf((float)(csc & 0xFFu), sc4.y, sc4.x) : 0.f;
+                        const float ie = fmaf((float)ci + (diff < 0.f ? 0.5f : -0.5f), sc4.w, sc4.z);
+                        const float A = (a.metric != 1) ? fmaf(diff, ie, gp) * inv_qn : diff * ie;
+                        float h = 0.f;
 #pragma unroll
-                                for (int i = 1; i <= 4; ++i)  // zero entries past L
-                                    h += tab[(int)((cw[0] >> ((i - 1) * 8)) & 0xFFu) * TW + i];
-                                int b = (int)(A * (float)kCompactLutBins);
-                                b = b < kCompactLutBins - 1 ? b : kCompactLutBins - 1;
-                                pass = h >= a.aux[b];
-                            }
-                        }
-                    } else if (cand) {
+                        for (int i = 1; i <= 4; ++i)  // zero entries past L
+                            h += tab[(int)((cw[0] >> ((i - 1) * 8)) & 0xFFu) * TW + i];
+                        int b = (int)(A * (float)kCompactLutBins);
+                        b = b < 0 ? 0 : (b < kCompactLutBins - 1 ? b : kCompactLutBins - 1);
+                        const bool zero = ci == 255u;
+                        const bool ge1 = !zero & (A >= 1.f), le0 = !zero & !ge1 & (A <= 0.f);
+                        kind = zero ? 0 : (ge1 ? 1 : (le0 ? 2 : 3));
+                        const bool hpass = h >= a.aux[b];
+                        pass = zero ? diff < 0.f : (ge1 ? false : (le0 ? true : hpass));
+                    } else {
                         // full precision: sg = g_e, se = |e|; halves: sg =
                         // g_e/|e|, se = 1/|e| (infinite for a zero edge).
                         // sg is zero for angular and inner product; the
@@ -871,8 +897,8 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                                             : num * __builtin_amdgcn_rcpf((a.metric != 1 ? qn : 1.f) * se);
                         // zero-length edge: the sign of the numerator; A_r >= 1
                         // fails, A_r <= 0 passes, otherwise H against T
-                        const bool ge1 = !zero && A >= 1.f;
-                        const bool le0 = !zero && !ge1 && A <= 0.f;
+                        const bool ge1 = !zero & (A >= 1.f);
+                        const bool le0 = !zero & !ge1 & (A <= 0.f);
                         kind = zero ? 0 : (ge1 ? 1 : (le0 ? 2 : 3));
                         bool hpass;
                         if (a.mode == 2) {
@@ -904,52 +930,31 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                         }
                         pass = zero ? num < 0.f : (ge1 ? false : (le0 ? true : hpass));
                     }
+                }
+                if (spilled) vis = valid && ((vw >> ((uint32_t)u & 31u)) & 1u);
+                lc_skip += vis ? 1 : 0;
+                const bool cand = valid && !vis;
+                pass = pass && cand;
+                if (testing) {
                     // every tested edge gets exactly one kind
+                    kind = cand ? kind : -1;
                     st_zero += popc(ballot(kind == 0));
                     lc_ge1 += kind == 1 ? 1 : 0;
                     lc_le0 += kind == 2 ? 1 : 0;
                     lc_h += kind == 3 ? 1 : 0;
                 }
-                const uint64_t smask = ballot(pass);
+                smask = ballot(pass);
                 const int ns = popc(smask);
                 st_pass += testing ? ns : 0;
                 km = 0;
                 if (ns == 0) {
                     if (!more) break;
                     vid = nid;
-                    dv = nd;
+                    dv = bits_value(nk);
                     continue;
                 }
 
-                // visited := visited + survivors
-                if (!spilled && nvis + ns > a.visit_limit) {
-                    if (bm_unknown) {
-                        for (int w = lane; w < (a.spill_bitmap_words >> 2); w += kWave)
-                            reinterpret_cast<uint4*>(bitmap)[w] = make_uint4(0u, 0u, 0u, 0u);
-                        wave_mem_order();
-                    }
-                    for (int t = lane; t < hcap; t += kWave) {
-                        const uint32_t k = hash[t];
-                        if (k != kEmpty) atomicOr(bitmap + (k >> 5), 1u << (k & 31u));
-                    }
-                    wave_mem_order();
-                    spilled = true;
-                    bm_unknown = true;
-                    nlist = 0;
-                    status |= kStatusSpill;
-                }
-                if (pass) {
-                    const int t = lanes_before(smask);
-                    if (spilled) {
-                        atomicOr(bitmap + ((uint32_t)u >> 5), 1u << ((uint32_t)u & 31u));
-                        if (nlist + t < a.spill_list_cap) slist[nlist + t] = (uint32_t)u;
-                    } else {
-                        hash_insert_at(hash, (uint32_t)hcap, (uint32_t)u, hfree);
-                    }
-                    Su[t] = (uint32_t)u;
-                }
-                if (spilled) nlist += ns;
-                nvis += ns;
+                if (pass) Su[lanes_before(smask)] = (uint32_t)u;
                 wave_sync();
                 lead_distances<BF, (MAXL >= 16) && BF, LONG>(nw, coop, tbase, d, Su, ns, qv, a.metric,
                                                              inv_qn, Sdist, kCoopTraversal);
@@ -960,36 +965,39 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 // (lane t = survivor t); the next node is the closest of
                 // them or the list's next
                 bool keep = false;
+                uint32_t ut = 0u, ob = 0xFFFFFFFFu;
                 if (lane < ns) {
-                    dt = Sdist[lane];
+                    const float dt = Sdist[lane];
                     ut = Su[lane];
                     keep = !full || dt < delta;
+                    if (keep) ob = order_bits(dt);
                 }
                 wave_sync();
                 km = ballot(keep);
+                surv = keep ? list_entry(ob, ut) : kNoEntry;
                 st_ins += popc(km);
                 if (km != 0) {
-                    const uint32_t ob = keep ? order_bits(dt) : 0xFFFFFFFFu;
                     const uint32_t om = wave_min(ob);
                     uint64_t tie = ballot(keep && ob == om);
-                    int t = __ffsll((unsigned long long)tie) - 1;
-                    uint32_t tid = (uint32_t)__builtin_amdgcn_readlane((int)ut, t);
-                    const float td = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dt), t));
+                    uint32_t tid = (uint32_t)__builtin_amdgcn_readlane((int)ut, __ffsll((unsigned long long)tie) - 1);
                     for (tie &= tie - 1; tie; tie &= tie - 1) {  // equal distances: the smaller id
-                        t = __ffsll((unsigned long long)tie) - 1;
-                        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)ut, t);
+                        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)ut, __ffsll((unsigned long long)tie) - 1);
                         tid = o < tid ? o : tid;
                     }
-                    const uint32_t on = order_bits(nd);
-                    if (!more || om < on || (om == on && tid < nid)) {
+                    if (!more || om < nk || (om == nk && tid < nid)) {
                         nid = tid;
-                        nd = td;
+                        nk = om;
                         more = true;
                     }
                 }
-                if (!more) break;
+                if (!more) {
+                    // (the last survivors need no entry in the visited set,
+                    // but count towards its limit)
+                    if (!spilled && nvis + ns > a.visit_limit) status |= kStatusSpill;
+                    break;
+                }
                 vid = nid;
-                dv = nd;
+                dv = bits_value(nk);
             }
             if (spilled && nlist <= a.spill_list_cap) {
                 // clear the words this query set: the ids the hash held at
@@ -1005,10 +1013,7 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
             }
             if (REGL) {
                 // the list to LDS for the output (and the re-rank)
-                if (lane < size) {
-                    Ld[lane] = rd;
-                    Li[lane] = ri;
-                }
+                if (lane < size) Le[lane] = re;
                 wave_sync();
             }
         } else {
@@ -1023,22 +1028,21 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
             const float inv_qn = 1.f / qn;
             for (int c0 = 0; c0 < nr; c0 += kWave) {
                 const int cnt = nr - c0 < kWave ? nr - c0 : kWave;
-                if (lane < cnt) Su[lane] = Li[c0 + lane] & kIdMask;
+                if (lane < cnt) Su[lane] = (uint32_t)Le[c0 + lane] >> 1;
                 wave_sync();
                 lead_distances<false, false, LONG>(nw, coop, a.base, d, Su, cnt, qv, a.metric, inv_qn,
                                                    Sdist, kCoopFull);
                 wave_sync();
-                if (lane < cnt) Ld[c0 + lane] = Sdist[lane];
+                if (lane < cnt) Le[c0 + lane] = list_entry(order_bits(Sdist[lane]), Su[lane]);
                 wave_sync();
             }
             for (int t = lane; t < nr; t += kWave) {
-                const uint32_t id = Li[t] & kIdMask;
-                const uint64_t key = sort_key(Ld[t], id);
+                const uint64_t e = Le[t];
                 int rank = 0;
-                for (int o = 0; o < nr; ++o) rank += sort_key(Ld[o], Li[o] & kIdMask) < key;
+                for (int o = 0; o < nr; ++o) rank += Le[o] < e;
                 if (rank < kq) {
-                    ca.ids[qi * kstride + rank] = (int64_t)id;
-                    ca.dists[qi * kstride + rank] = Ld[t];
+                    ca.ids[qi * kstride + rank] = (int64_t)((uint32_t)e >> 1);
+                    ca.dists[qi * kstride + rank] = bits_value((uint32_t)(e >> 32));
                 }
             }
             const int kout = kq < nr ? kq : nr;
@@ -1050,8 +1054,9 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
             // results: first k entries of the list, padded with (-1, +inf)
             for (int t = lane; t < kstride; t += kWave) {
                 const bool ok = t < kq && t < size;
-                ca.ids[qi * kstride + t] = ok ? (int64_t)(Li[t] & kIdMask) : (int64_t)-1;
-                ca.dists[qi * kstride + t] = ok ? Ld[t] : INFINITY;
+                const uint64_t e = ok ? Le[t] : kNoEntry;
+                ca.ids[qi * kstride + t] = ok ? (int64_t)((uint32_t)e >> 1) : (int64_t)-1;
+                ca.dists[qi * kstride + t] = ok ? bits_value((uint32_t)(e >> 32)) : INFINITY;
             }
         }
         const int st_skip = wave_sum_int(lc_skip), st_ge1 = wave_sum_int(lc_ge1);

@@ -10,8 +10,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // empty visited-hash slot
-constexpr uint32_t kExpanded = 0x80000000u; // "expanded" flag on a list id
-constexpr uint32_t kIdMask = 0x7FFFFFFFu;
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
@@ -132,9 +130,14 @@ __device__ __forceinline__ uint32_t order_bits(float f)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+__device__ __forceinline__ float bits_value(uint32_t k)
+{
+    return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
+}
+
 __device__ __forceinline__ uint64_t sort_key(float d, uint32_t id)
 {
-    return (static_cast<uint64_t>(order_bits(d)) << 32) | (id & kIdMask);
+    return (static_cast<uint64_t>(order_bits(d)) << 32) | id;
 }
 
 }  // namespace peos
