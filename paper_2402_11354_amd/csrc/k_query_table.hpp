@@ -13,6 +13,8 @@
 // The precision form stores the table as halves.
 #pragma once
 
+#include <type_traits>
+
 #include "peos_device.hpp"
 
 namespace peos {
@@ -38,6 +40,7 @@ struct QueryTableArgs {
 // are dealt out to the waves.  With staged rows and no permutation both
 // operands are read 16 bytes per lane: a group of four K steps per load.
 constexpr int kTableWaves = 4;
+constexpr int kWideWaves = 8;  // of the body for m > 16
 
 // |q| of this lane's row (lane % 16) from the staged rows:
 // sqrt((p0 + p1) + (p2 + p3)), p_j the fma chain of q_k^2 over k = j mod 4
@@ -278,7 +281,156 @@ __device__ __forceinline__ void query_table16(const QueryTableArgs& a, float* qs
     }
 }
 
-__global__ __launch_bounds__(kTableWaves * 64) void k_query_table(QueryTableArgs a)
+// m > 16, staged rows, no permutation: the (L + 1) m / 16 output tiles of a
+// block of 16 queries are dealt to the waves of gridDim.y workgroups by their
+// number of K steps (a full-space tile counts as L subspace tiles: it is one
+// chain and is not split), so that a few queries with many directions fill the
+// chip.  Every tile keeps its chain of MFMAs in the order of K, so the table
+// does not depend on the split.  Subspace tiles go four at a time, full-space
+// tiles one at a time, the next group's operands loaded before a group's
+// MFMAs; wave 0 takes the norms before its tiles, and the one barrier stands
+// between the first tiles' MFMAs and their stores.
+// What bounds it: the directions are read from L2 once per 16 queries, 1 MB
+// at m = 128, d = 960; 2,049 queries there took 66.6 us with one workgroup
+// per 16 queries and a load's latency before every 16 MFMAs.
+__device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const float* qs, float* inv_norm,
+                                                 int nrows, int64_t q0, int wv, int lane)
+{
+#pragma clang fp contract(off)
+    const int d = a.d, L = a.L, m = a.m, mt = m >> 4;
+    const int dp = d / L;
+    const int row = lane & 15;
+    const int kq = lane >> 4;
+    const float* ql = qs + row * (d + 4);
+
+    if (wv == 0) {
+        const float nrm = staged_row_norm(ql, d, kq);
+        if (kq == 0) {
+            inv_norm[row] = (nrm > 0.f && nrm < INFINITY) ? 1.f / nrm : 0.f;
+            if (blockIdx.y == 0 && row < nrows) a.qnorms[q0 + row] = nrm;
+        }
+    }
+    // this wave's tiles: work units [u0, u1) of the 2 L mt of the block, the
+    // full-space tiles' L units each first; a tile belongs to the wave that
+    // holds its first unit
+    const int nw = kWideWaves * (int)gridDim.y, w = (int)blockIdx.y * kWideWaves + wv;
+    const int U = 2 * L * mt;
+    const int u0 = (int)((int64_t)U * w / nw), u1 = (int)((int64_t)U * (w + 1) / nw);
+    const int nf = L * mt;  // units of the full-space tiles
+    const int f0 = ((u0 < nf ? u0 : nf) + L - 1) / L, f1 = ((u1 < nf ? u1 : nf) + L - 1) / L;
+    const int s0 = u0 > nf ? u0 - nf : 0, s1 = u1 > nf ? u1 - nf : 0;  // subspace tiles (i - 1) mt + j
+
+    auto store = [&](const floatx4& v, int i, int j) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int orow = 4 * kq + r;
+            if (orow < nrows) {
+                const float tv = v[r] * inv_norm[orow];
+                const int64_t o = ((q0 + orow) * (L + 1) + i) * m + 16 * j + row;
+                if (a.half_out) reinterpret_cast<_Float16*>(a.tables)[o] = (_Float16)tv;
+                else a.tables[o] = tv;
+            }
+        }
+    };
+    // one chain over K = len of each of N tiles, in groups of 16 (step c of
+    // group g: k = 16 g + 4 (lane / 16) + c for both operands), then the last
+    // len mod 16 step by step.  G groups of every tile (N G = 4) are requested
+    // while the G before them are multiplied; the query operand comes from LDS
+    // as it is used.
+    auto chains = [&](auto tiles, const auto& av, const auto& bv, int len, auto& acc) __attribute__((always_inline)) {
+        constexpr int N = decltype(tiles)::value, G = 4 / N;
+        float4 bq[2][G][N];
+        const int ng = len >> 4;
+        auto load = [&](int h, int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    bq[h][j][u] = *reinterpret_cast<const float4*>(bv[u] + 16 * (g + j < ng ? g + j : ng - 1) + 4 * kq);
+        };
+        auto mul = [&](int h, int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                if (G > 1 && g + j >= ng) break;
+                float4 aq[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) aq[u] = *reinterpret_cast<const float4*>(av[u] + 16 * (g + j) + 4 * kq);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].x, bq[h][j][u].x, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].y, bq[h][j][u].y, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].z, bq[h][j][u].z, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].w, bq[h][j][u].w, acc[u], 0, 0, 0);
+            }
+        };
+        // the remainder's operands (at most three steps), requested first
+        const int nr = (len - 16 * ng) >> 2;
+        float br[3][N];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int u = 0; u < N; ++u) br[q][u] = q < nr ? bv[u][16 * ng + 4 * q + kq] : 0.f;
+        if (ng > 0) load(0, 0);
+        for (int g = 0; g < ng; g += 2 * G) {
+            if (g + G < ng) load(1, g + G);
+            mul(0, g);
+            if (g + G < ng) {
+                if (g + 2 * G < ng) load(0, g + 2 * G);
+                mul(1, g + G);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            if (q < nr)
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][16 * ng + 4 * q + kq], br[q][u], acc[u], 0, 0, 0);
+    };
+
+    bool waited = false;
+    auto wait_norms = [&]() {
+        if (!waited) __syncthreads();
+        waited = true;
+    };
+    for (int t = f0; t < f1; ++t) {
+        floatx4 acc[1] = {floatx4{0.f, 0.f, 0.f, 0.f}};
+        const float* av[1] = {ql};
+        const float* bv[1] = {a.dirs_b + (int64_t)(16 * t + row) * d};
+        chains(std::integral_constant<int, 1>(), av, bv, d, acc);
+        wait_norms();
+        store(acc[0], 0, t);
+    }
+    for (int t = s0; t < s1; t += 4) {
+        floatx4 acc[4];
+        const float* av[4];
+        const float* bv[4];
+        int ti[4], tj[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = t + u < s1 ? t + u : s1 - 1;  // (a slot past the last repeats it, not stored)
+            ti[u] = v / mt;
+            tj[u] = v - ti[u] * mt;
+            bv[u] = a.dirs_a + ((int64_t)ti[u] * m + 16 * tj[u] + row) * dp;
+            av[u] = ql + ti[u] * dp;
+            acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        chains(std::integral_constant<int, 4>(), av, bv, dp, acc);
+        wait_norms();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t + u < s1) store(acc[u], 1 + ti[u], tj[u]);
+    }
+    wait_norms();
+}
+
+// the three bodies as kernels of their own (each with its own registers)
+enum TableBody { kTable16, kTableWide, kTableGeneral };
+
+template <int BODY>
+__global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 64,
+                             BODY == kTableWide ? 4 : 1) void k_query_table(QueryTableArgs a)
 {
 #pragma clang fp contract(off)
     extern __shared__ __align__(16) float qs[];  // 16 x (d + 4)
@@ -297,7 +449,27 @@ __global__ __launch_bounds__(kTableWaves * 64) void k_query_table(QueryTableArgs
     // operands are read).  Past 16 (d + 4) floats of LDS the rows are read
     // from global memory instead.
     const int nch = d >> 2;
-    if (a.staged) {
+    if constexpr (BODY == kTableWide) {
+        // two rows a wave, their loads in flight together
+        static_assert(2 * kWideWaves == 16, "two rows a wave");
+        const int r0 = wv < nrows ? wv : 0, r1 = wv + kWideWaves < nrows ? wv + kWideWaves : 0;
+        const float4* p0 = reinterpret_cast<const float4*>(a.queries + (q0 + r0) * (int64_t)d);
+        const float4* p1 = reinterpret_cast<const float4*>(a.queries + (q0 + r1) * (int64_t)d);
+        const bool in0 = wv < nrows, in1 = wv + kWideWaves < nrows;
+        auto put = [](float4* w, float4 v, bool in) {
+            *w = make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f);
+        };
+        float4* w0 = reinterpret_cast<float4*>(qs + wv * ld);
+        float4* w1 = reinterpret_cast<float4*>(qs + (wv + kWideWaves) * ld);
+        for (int k = lane; k < nch; k += 2 * kWave) {
+            const int k2 = k + kWave < nch ? k + kWave : k;
+            const float4 v0 = p0[k], v1 = p1[k], v2 = p0[k2], v3 = p1[k2];
+            put(w0 + k, v0, in0);
+            put(w1 + k, v1, in1);
+            put(w0 + k2, v2, in0);
+            put(w1 + k2, v3, in1);
+        }
+    } else if (a.staged) {
         for (int c = tid; c < 16 * nch; c += kTableWaves * 64) {
             const int r = c / nch, k4 = (c - r * nch) * 4;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -307,8 +479,12 @@ __global__ __launch_bounds__(kTableWaves * 64) void k_query_table(QueryTableArgs
         }
     }
     __syncthreads();
-    if (a.staged && !a.perm && m == 16) {
+    if constexpr (BODY == kTable16) {
         query_table16(a, qs, nrows, q0, wv, lane);
+        return;
+    }
+    if constexpr (BODY == kTableWide) {
+        query_table_wide(a, qs, inv_norm, nrows, q0, wv, lane);
         return;
     }
 
@@ -344,45 +520,6 @@ __global__ __launch_bounds__(kTableWaves * 64) void k_query_table(QueryTableArgs
     const int col = lane & 15;
     const int kb = lane >> 4;
     const int ntile = (L + 1) * (m >> 4);
-    const bool fast = a.staged && !a.perm;
-
-    // staged rows, no permutation: K in groups of 16, each one 16-byte load
-    // per lane for either operand.  Within group j, step 4j + c takes
-    // k = 16j + 4 (lane/16) + c from both operands (any assignment of the k
-    // to the steps gives the same sum up to rounding, as long as A and B
-    // agree).  Four groups' loads are issued before their MFMAs; then the
-    // last k_len mod 16 step by step (k = k0 + lane/16).
-    auto fast_tile = [&](floatx4 acc, int k_begin, const float* bv, int k_len) {
-        const float* ql = qs + row * ld + k_begin;  // (an LDS pointer, so LDS reads)
-        const int g1 = k_len >> 4;
-        int j = 0;
-        for (; j + 4 <= g1; j += 4) {
-            float4 bq[4], aq[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bq[u] = *reinterpret_cast<const float4*>(bv + 16 * (j + u) + 4 * kb);
-                aq[u] = *reinterpret_cast<const float4*>(ql + 16 * (j + u) + 4 * kq);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].x, bq[u].x, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].y, bq[u].y, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].z, bq[u].z, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].w, bq[u].w, acc, 0, 0, 0);
-            }
-        }
-        for (; j < g1; ++j) {
-            const float4 bq = *reinterpret_cast<const float4*>(bv + 16 * j + 4 * kb);
-            const float4 aq = *reinterpret_cast<const float4*>(ql + 16 * j + 4 * kq);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.x, bq.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.y, bq.y, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.z, bq.z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aq.w, bq.w, acc, 0, 0, 0);
-        }
-        for (int k0 = 16 * g1; k0 < k_len; k0 += 4)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ql[k0 + kq], bv[k0 + kb], acc, 0, 0, 0);
-        return acc;
-    };
 
     for (int t = wv; t < ntile; t += kTableWaves) {
         const int i = t / (m >> 4);
@@ -397,21 +534,17 @@ __global__ __launch_bounds__(kTableWaves * 64) void k_query_table(QueryTableArgs
             return qget(a.perm ? a.perm[kk] : kk);
         };
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (fast) {
-            acc = fast_tile(acc, k_begin, bv, k_len);
-        } else {
-            int k0 = 0;
-            for (; k0 + 32 <= k_len; k0 += 32) {
-                float bb[8];
+        int k0 = 0;
+        for (; k0 + 32 <= k_len; k0 += 32) {
+            float bb[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) bb[u] = bv[k0 + 4 * u + kb];
+            for (int u = 0; u < 8; ++u) bb[u] = bv[k0 + 4 * u + kb];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0 + 4 * u), bb[u], acc, 0, 0, 0);
-            }
-            for (; k0 < k_len; k0 += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0), bv[k0 + kb], acc, 0, 0, 0);
+            for (int u = 0; u < 8; ++u)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0 + 4 * u), bb[u], acc, 0, 0, 0);
         }
+        for (; k0 < k_len; k0 += 4)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0), bv[k0 + kb], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int orow = 4 * (lane >> 4) + r;

@@ -249,8 +249,11 @@ int ensure_kernel_attrs(int dev)
 #undef PEOS_FNS
         for (const void* f : fns)
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
-        HIP_TRY(hipFuncSetAttribute((const void*)peos::k_query_table,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
+        const void* tables[] = {(const void*)peos::k_query_table<peos::kTable16>,
+                                (const void*)peos::k_query_table<peos::kTableWide>,
+                                (const void*)peos::k_query_table<peos::kTableGeneral>};
+        for (const void* f : tables)
+            HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
         done[dev] = true;
     }
     return PEOS_OK;
@@ -781,8 +784,21 @@ int peos_query_tables(const peos_index* ix, const float* queries, int64_t nq, fl
     const size_t lds = a.staged ? std::max(tile, parts) : 0;
     int rc = ensure_kernel_attrs(ix->device);
     if (rc) return rc;
-    hipLaunchKernelGGL(peos::k_query_table, dim3((unsigned)blocks), dim3(64 * peos::kTableWaves),
-                       lds, (hipStream_t)stream, a);
+    const dim3 block(64 * peos::kTableWaves);
+    hipStream_t s = (hipStream_t)stream;
+    if (!a.staged || a.perm) {
+        hipLaunchKernelGGL(peos::k_query_table<peos::kTableGeneral>, dim3((unsigned)blocks), block, lds, s, a);
+    } else if (a.m == 16) {
+        hipLaunchKernelGGL(peos::k_query_table<peos::kTable16>, dim3((unsigned)blocks), block, lds, s, a);
+    } else {
+        // as many workgroups per 16 queries as are resident at once (two a
+        // CU at d = 960), each wave with at least a full-space tile's work
+        const int64_t want = 2 * (int64_t)ix->num_cu / blocks;
+        const int64_t most = (2 * (int64_t)(a.m / 16) + peos::kWideWaves - 1) / peos::kWideWaves;
+        const unsigned split = (unsigned)std::max<int64_t>(1, std::min(want, most));
+        hipLaunchKernelGGL(peos::k_query_table<peos::kTableWide>, dim3((unsigned)blocks, split),
+                           dim3(64 * peos::kWideWaves), lds, s, a);
+    }
     HIP_TRY(hipGetLastError());
     return PEOS_OK;
 }
