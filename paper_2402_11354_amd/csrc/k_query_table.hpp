@@ -335,34 +335,41 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
     // one chain over K = len of each of N tiles, in groups of 16 (step c of
     // group g: k = 16 g + 4 (lane / 16) + c for both operands), then the last
     // len mod 16 step by step.  G groups of every tile (N G = 4) are requested
-    // while the G before them are multiplied; the query operand comes from LDS
-    // as it is used.
+    // while the G before them are multiplied, 64 bytes of a direction by four
+    // lanes (by_row); the query operand comes from LDS as it is used.  bv: a
+    // tile's first direction.
     auto chains = [&](auto tiles, const auto& av, const auto& bv, int len, auto& acc) __attribute__((always_inline)) {
         constexpr int N = decltype(tiles)::value, G = 4 / N;
-        float4 bq[2][G][N];
         const int ng = len >> 4;
-        auto load = [&](int h, int g) __attribute__((always_inline)) {
+        auto load = [&](float4 (&b)[G][N], int g) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < G; ++j)
 #pragma unroll
                 for (int u = 0; u < N; ++u)
-                    bq[h][j][u] = *reinterpret_cast<const float4*>(bv[u] + 16 * (g + j < ng ? g + j : ng - 1) + 4 * kq);
+                    b[j][u] = *reinterpret_cast<const float4*>(bv[u] + (lane >> 2) * len +
+                                                               16 * (g + j < ng ? g + j : ng - 1) + 4 * (lane & 3));
         };
-        auto mul = [&](int h, int g) __attribute__((always_inline)) {
+        // n groups from g on (all operands first, then the MFMAs)
+        auto mul = [&](float4 (&b)[G][N], int g, int n) __attribute__((always_inline)) {
+            float4 aq[G][N];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    b[j][u] = by_row(b[j][u]);
+                    aq[j][u] = *reinterpret_cast<const float4*>(av[u] + 16 * (g + j < ng ? g + j : ng - 1) + 4 * kq);
+                }
 #pragma unroll
             for (int j = 0; j < G; ++j) {
-                if (G > 1 && g + j >= ng) break;
-                float4 aq[N];
+                if (j >= n) break;
 #pragma unroll
-                for (int u = 0; u < N; ++u) aq[u] = *reinterpret_cast<const float4*>(av[u] + 16 * (g + j) + 4 * kq);
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[j][u].x, b[j][u].x, acc[u], 0, 0, 0);
 #pragma unroll
-                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].x, bq[h][j][u].x, acc[u], 0, 0, 0);
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[j][u].y, b[j][u].y, acc[u], 0, 0, 0);
 #pragma unroll
-                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].y, bq[h][j][u].y, acc[u], 0, 0, 0);
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[j][u].z, b[j][u].z, acc[u], 0, 0, 0);
 #pragma unroll
-                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].z, bq[h][j][u].z, acc[u], 0, 0, 0);
-#pragma unroll
-                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[u].w, bq[h][j][u].w, acc[u], 0, 0, 0);
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(aq[j][u].w, b[j][u].w, acc[u], 0, 0, 0);
             }
         };
         // the remainder's operands (at most three steps), requested first
@@ -371,14 +378,21 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
 #pragma unroll
         for (int q = 0; q < 3; ++q)
 #pragma unroll
-            for (int u = 0; u < N; ++u) br[q][u] = q < nr ? bv[u][16 * ng + 4 * q + kq] : 0.f;
-        if (ng > 0) load(0, 0);
-        for (int g = 0; g < ng; g += 2 * G) {
-            if (g + G < ng) load(1, g + G);
-            mul(0, g);
-            if (g + G < ng) {
-                if (g + 2 * G < ng) load(0, g + 2 * G);
-                mul(1, g + G);
+            for (int u = 0; u < N; ++u) br[q][u] = q < nr ? bv[u][row * len + 16 * ng + 4 * q + kq] : 0.f;
+        if (ng > 0) {
+            float4 b0[G][N], b1[G][N];
+            load(b0, 0);
+            int g = 0;
+            for (; g + 2 * G <= ng; g += 2 * G) {
+                load(b1, g + G);
+                mul(b0, g, G);
+                load(b0, g + 2 * G);  // (past the end: the last group again, not used)
+                mul(b1, g + G, G);
+            }
+            if (g < ng) {
+                load(b1, g + G);
+                mul(b0, g, ng - g);
+                if (g + G < ng) mul(b1, g + G, ng - g - G);
             }
         }
 #pragma unroll
@@ -397,7 +411,7 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
     for (int t = f0; t < f1; ++t) {
         floatx4 acc[1] = {floatx4{0.f, 0.f, 0.f, 0.f}};
         const float* av[1] = {ql};
-        const float* bv[1] = {a.dirs_b + (int64_t)(16 * t + row) * d};
+        const float* bv[1] = {a.dirs_b + (int64_t)(16 * t) * d};
         chains(std::integral_constant<int, 1>(), av, bv, d, acc);
         wait_norms();
         store(acc[0], 0, t);
@@ -412,7 +426,7 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
             const int v = t + u < s1 ? t + u : s1 - 1;  // (a slot past the last repeats it, not stored)
             ti[u] = v / mt;
             tj[u] = v - ti[u] * mt;
-            bv[u] = a.dirs_a + ((int64_t)ti[u] * m + 16 * tj[u] + row) * dp;
+            bv[u] = a.dirs_a + ((int64_t)ti[u] * m + 16 * tj[u]) * dp;
             av[u] = ql + ti[u] * dp;
             acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
         }

@@ -63,6 +63,19 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int t)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// 64 bytes a row by four lanes: lane l of the load holds 16-byte chunk l % 4
+// of row l / 4 (consecutive lanes share a row, so the 64 bytes are one
+// access; with a row per lane of 16 every lane's 16 bytes are an access of
+// their own, and the vector caches serve one a cycle).  by_row moves them to
+// the matrix cores' layout: lane 16 c + r receives chunk c of row r.
+__device__ __forceinline__ float4 by_row(float4 v)
+{
+    const int l = lane_id();
+    const int from = 4 * (4 * (l & 15) + (l >> 4));
+    auto move = [&](float x) { return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(x))); };
+    return make_float4(move(v.x), move(v.y), move(v.z), move(v.w));
+}
+
 // value of v in lane (this lane xor O), all lanes active: lane swaps within
 // quads are DPP moves (no LDS round trip), xor 4 / 8 / 16 a swizzle, wider
 // ones a permute through the LDS crossbar
