@@ -177,19 +177,6 @@ __device__ __forceinline__ void hash_insert(uint32_t* h, uint32_t cap, uint32_t 
     }
 }
 
-// insert of a key whose lookup (nothing inserted since but by the other lanes
-// of this round) named a free slot: it, or the next ones of its bucket where
-// other lanes of the round came first; without a second look at the buckets
-__device__ __forceinline__ void hash_insert_at(uint32_t* h, uint32_t cap, uint32_t u, int free)
-{
-    if (free >= 0) {
-        do {
-            if (atomicCAS(&h[free], kEmpty, u) == kEmpty) return;
-        } while ((++free & 3) != 0);
-    }
-    hash_insert(h, cap, u);
-}
-
 // the word of the bitmap that holds u's bit
 __device__ __forceinline__ uint32_t bitmap_word(const uint32_t* bm, uint32_t u)
 {
@@ -598,6 +585,7 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
             uint64_t smask = 0;
             int hfree = -1;
             for (;;) {
+                const uint32_t us = Su[lanes_before(smask)];  // (of a survivor's lane)
                 const int nS = popc(km);
                 const bool full = size + nS >= efq;
                 const bool testing = tests && full;
@@ -644,12 +632,14 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 }
 
                 // visited := visited + the last expansion's survivors (while
-                // the loads above are in flight)
+                // the loads above are in flight): each asks for the free slot
+                // its lookup saw, and the few that lost it to another lane of
+                // the round, or saw none, insert with a second look below,
+                // after the merge
+                const bool fresh = (smask >> lane) & 1u;
+                uint32_t held = kEmpty;  // what the slot held
                 if (smask != 0) {
                     const int ns = popc(smask);
-                    const bool pass = (smask >> lane) & 1u;
-                    const int t = lanes_before(smask);
-                    const uint32_t us = Su[t];
                     if (!spilled && nvis + ns > a.visit_limit) {
                         if (bm_unknown) {
                             for (int w = lane; w < (a.spill_bitmap_words >> 2); w += kWave)
@@ -666,17 +656,18 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                         nlist = 0;
                         status |= kStatusSpill;
                     }
-                    if (pass) {
-                        if (spilled) {
+                    if (spilled) {
+                        if (fresh) {
+                            const int t = nlist + lanes_before(smask);
                             atomicOr(bitmap + (us >> 5), 1u << (us & 31u));
-                            if (nlist + t < a.spill_list_cap) slist[nlist + t] = us;
-                        } else {
-                            hash_insert_at(hash, (uint32_t)hcap, us, hfree);
+                            if (t < a.spill_list_cap) slist[t] = us;
                         }
+                        nlist += ns;
+                        smask = 0;
+                    } else if (fresh) {
+                        held = hfree < 0 ? us : atomicCAS(&hash[hfree], kEmpty, us);
                     }
-                    if (spilled) nlist += ns;
                     nvis += ns;
-                    wave_sync();
                 }
 
                 // merge of the last expansion's survivors
@@ -721,7 +712,8 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
 #pragma unroll
                             for (int c = 0; c < N; ++c) {
                                 const int p = b0 + c * kWave + lane;
-                                e[c] = p < size ? Le[p] : kNoEntry;
+                                e[c] = Le[p];  // (room for whole chunks; past the last entry: dropped)
+                                if (p >= size) e[c] = kNoEntry;
                                 sh[c] = 0;
                             }
                             int least = N * kWave;
@@ -742,10 +734,9 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                             wave_sync();
 #pragma unroll
                             for (int c = 0; c < N; ++c) {
-                                const int p = b0 + c * kWave + lane;
-                                const bool in = p < size && sh[c] != 0;
-                                drop |= in && p < efq && p + sh[c] >= efq && (e[c] & 1u);
-                                if (in && p + sh[c] < cap + slack) Le[p + sh[c]] = e[c];
+                                const int p = b0 + c * kWave + lane, to = p + sh[c];
+                                if (cap > efq) drop |= (p < efq) & (to >= efq) & ((uint32_t)e[c] & 1u) & (p < size);
+                                if ((sh[c] != 0) & (p < size) & (to < cap + slack)) Le[to] = e[c];
                             }
                             wave_sync();
                             return least;
@@ -754,6 +745,7 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                         int least;
                         if (size - b0 <= kWave) least = merge_block(std::integral_constant<int, 1>(), b0, true);
                         else if (size - b0 <= 2 * kWave) least = merge_block(std::integral_constant<int, 2>(), b0, true);
+                        else if (size - b0 <= 3 * kWave) least = merge_block(std::integral_constant<int, 3>(), b0, true);
                         else least = merge_block(std::integral_constant<int, 4>(), b0, true);
                         while (b0 > 0 && least == 0) {
                             b0 -= 4 * kWave;
@@ -787,13 +779,14 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                         }
                         if (w > cap && pool == 0) status |= kStatusPoolFull;
                         size = w < cap ? w : cap;
-                        // the first survivor's place
-                        for (uint64_t mm = km; mm; mm &= mm - 1) {
-                            const int l = __builtin_amdgcn_readlane(lo, __ffsll((unsigned long long)mm) - 1);
-                            lb = l < lb ? l : lb;
-                        }
+                        lb = b0 + least < lb ? b0 + least : lb;  // the first survivor's place
                     }
                 }
+                if (smask != 0) {
+                    if (held != kEmpty) hash_insert(hash, (uint32_t)hcap, us);
+                    wave_sync();
+                }
+
                 // the popped entry is marked, and the entry that comes next
                 // if no survivor of this expansion comes before it is found
                 uint32_t nid = 0u, nk = 0u;
@@ -814,12 +807,12 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                     // second
                     more = false;
                     bool seen = false;
-                    int c0 = lb;
+                    int c0 = lb & ~(kWave - 1);  // (whole chunks: none reads past the list's room)
                     lb = size;
                     for (; c0 < size; c0 += kWave) {
                         const int p = c0 + lane;
-                        const uint64_t e = p < size ? Le[p] : kNoEntry;
-                        uint64_t mk = ballot(!(e & 1u));
+                        const uint64_t e = Le[p];  // (past the last entry: dropped)
+                        uint64_t mk = ballot((p < size) & !((uint32_t)e & 1u));
                         if (mk && !seen) {
                             const int t = __ffsll((unsigned long long)mk) - 1;
                             if (lane == t) Le[p] = e | 1u;
