@@ -783,7 +783,11 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                     }
                 }
                 if (smask != 0) {
-                    if (held != kEmpty) hash_insert(hash, (uint32_t)hcap, us);
+                    // (the bucket's next slots first, filled front to back)
+                    bool in = held == kEmpty;
+                    if (!in && hfree >= 0)
+                        while (!in && (++hfree & 3) != 0) in = atomicCAS(&hash[hfree], kEmpty, us) == kEmpty;
+                    if (!in) hash_insert(hash, (uint32_t)hcap, us);
                     wave_sync();
                 }
 
