@@ -17,6 +17,7 @@
 #pragma once
 
 #include <deque>
+#include <thread>
 #include <vector>
 
 namespace {
@@ -341,17 +342,15 @@ int peos_serve_poll(peos_server* sv, int32_t wait, uint64_t* done, int32_t max_d
     int rc = serve_reap(sv, &any);
     if (rc) return rc;
     if (wait && !any && sv->finished.empty()) {
-        // block on the batch issued first among those in flight
-        ServeSlot* first = nullptr;
-        for (ServeSlot& s : sv->slots)
-            if (s.busy) {
-                first = &s;
-                break;
-            }
-        if (first) {
-            HIP_TRY(hipEventSynchronize(first->done));
+        // until any batch in flight is done, whichever slot it is in: its
+        // slot takes the requests that wait (blocking on one slot's event
+        // left the other slots empty behind a long batch)
+        bool busy = false;
+        for (const ServeSlot& s : sv->slots) busy |= s.busy;
+        while (busy && !any) {
             rc = serve_reap(sv, &any);
             if (rc) return rc;
+            if (!any) std::this_thread::yield();
         }
     }
     rc = serve_dispatch(sv);
