@@ -320,8 +320,12 @@ __device__ __forceinline__ void distances(const void* base, int d, const uint32_
     // variant keeps two such rows per lane group in flight: one round trip
     // per 8 vectors of up to 1024 coordinates, fp32 or bfloat16 (it is
     // only launched for d > 512, and is correct for any d).
+    // Up to 4 rows take one such row per lane group: an idle second row is
+    // loaded and multiplied like any other, half the vector instructions of a
+    // gather (two waves share a query's 8.6 survivors at d = 960).
     if (LONG) {
-        gather_distances<16, 2, 16, BF, true>(base, d, Su, ns, qv, metric, inv_qn, Sdist);
+        if (ns <= 4) gather_distances<16, 1, 16, BF, true>(base, d, Su, ns, qv, metric, inv_qn, Sdist);
+        else gather_distances<16, 2, 16, BF, true>(base, d, Su, ns, qv, metric, inv_qn, Sdist);
         return;
     }
     if (WIDE && d > 512) {
