@@ -7,18 +7,29 @@
 //         T_i[j] at j and -T_i[j] at m + j, so a code byte indexes it directly;
 //   list  the candidate list, sorted by (distance, id): its first ef entries
 //         are the result list R, entries beyond are nodes of the priority
-//         queue P that were pushed out of R before being expanded.  Ids carry
-//         an "expanded" bit.  Popping P = the first unexpanded entry;
+//         queue P that were pushed out of R before being expanded.  An entry
+//         is one 64-bit number (list_entry), its lowest bit "expanded".
+//         Popping P = the first unexpanded entry;
 //   hash  the visited set (open addressing), moved to a per-slot bitmap in
 //         HBM if it fills up.
 // Per expansion of v (delta read once, before the neighbours are tested):
-//   lane j < R loads neighbour id j of v and, when R is full and the test is
-//   on, edge j's L+1 code bytes and four scalars (all three loads depend on v
-//   only, so they are issued together, the id first); visited filter;
-//   routing test of step (6); survivors are marked visited and their vectors
-//   gathered by groups of lanes (64/ns... lanes per vector, so every
-//   survivor's load is in flight at once); survivors closer than delta (or
-//   all, while R is not full) are merged into the list.
+//   lane j < R requests neighbour id j of v and, when R is full and the test
+//   is on, edge j's L+1 code bytes and four scalars (all depend on v only, so
+//   they are issued together, the id first); while they are in flight, the
+//   last expansion's survivors enter the visited set and the list, v is
+//   marked and the entry after it found; visited filter and routing test of
+//   step (6), side by side; the survivors' vectors gathered by groups of
+//   lanes (64/ns... lanes per vector, so every survivor's load is in flight
+//   at once); survivors closer than delta (or all, while R is not full) and
+//   the list's next entry decide the next v.
+//
+// What one expansion costs (cycles of a wave at 2.4 GHz, measured phase by
+// phase; 1M x 128, ef = 64, one query alone / 10,000 at once): loads and
+// visited set 460 / 540, merge and pop 1270 / 1570, wait for the ids 30 / 230,
+// filter and test 1170 / 1420, gather 2210 / 4200, next node 460 / 570.  With
+// the merge and the pop before the loads, and lists in LDS compared entry by
+// entry, the chain was 207 us for one query of 78 expansions (188 now), 1.26
+// ms for 10,000 (1.16) and 2.95 ms for 4,000 at k = 100, ef = 200 (2.38).
 #pragma once
 
 #include <type_traits>
