@@ -872,8 +872,12 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
                 // it), so that neither waits for the other
                 bool vis = false;
                 uint32_t vw = 0u;
-                if (spilled) vw = bitmap_word(bitmap, (uint32_t)(valid ? u : 0));
-                else vis = hash_lookup(hash, (uint32_t)hcap, (uint32_t)u, valid, hfree);
+                if (spilled) {
+                    // (the last survivors' bits first: the merge above covers
+                    // most of what their atomics take)
+                    wave_mem_order();
+                    vw = bitmap_word(bitmap, (uint32_t)(valid ? u : 0));
+                } else vis = hash_lookup(hash, (uint32_t)hcap, (uint32_t)u, valid, hfree);
                 bool pass = true;
                 int kind = -1;
                 if (testing) {

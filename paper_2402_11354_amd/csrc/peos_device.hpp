@@ -27,13 +27,15 @@ __device__ __forceinline__ void wave_sync()
 
 // Ordering point for one wave's own global-memory accesses (the visited
 // bitmap and its cleanup list, which only the wave that searches the query
-// touches).  A wave's accesses to one address reach memory in issue order,
-// so no cache write-back or invalidation is needed (an agent-scope fence
-// would write back the whole L2 of the XCD, at every spill); this keeps the
-// compiler from moving accesses across it and orders the wave's lanes.
+// touches): the fence keeps the compiler from moving accesses across it, and
+// the wait holds the wave until those issued before are complete, so that a
+// lane reads what another lane's atomic or store put there, whatever order
+// the caches serve requests in.  No cache is written back or invalidated (an
+// agent-scope fence would write back the whole L2 of the XCD, at every spill).
 __device__ __forceinline__ void wave_mem_order()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0; the other counters at their maxima
     __builtin_amdgcn_wave_barrier();
 }
 
