@@ -224,9 +224,10 @@ int peos_dimension_permutation(const float* base, int64_t n, int32_t d, const in
  *                 coordinates (the permutation changes neither the graph nor
  *                 the guarantee).  Kept by the index: must stay valid until
  *                 peos_free.  Not with PEOS_FLAG_SIMHASH.
- *   simhash_dirs  device, 64 x d float, required by PEOS_FLAG_SIMHASH: the
- *                 sign-projection vectors of the SimHash test (kept by the
- *                 index: the search projects each query on them).
+ *   simhash_dirs  device, 64 x d float at any float's address, required by
+ *                 PEOS_FLAG_SIMHASH: the sign-projection vectors of the
+ *                 SimHash test (kept by the index: the search projects each
+ *                 query on them).
  * Errors as peos_build_tables.
  */
 typedef struct {

@@ -285,10 +285,12 @@ __global__ __launch_bounds__(64, MT <= 2 ? 4 : 3) void k_edge_build(EdgeBuildArg
         return make_float4(x[a.perm[k]], x[a.perm[k + 1]], x[a.perm[k + 2]], x[a.perm[k + 3]]);
     };
     // four steps (coordinates k .. k + 15) of a tile of 16 directions of
-    // `len` coordinates each, in step order (zeros from len on)
+    // `len` coordinates each, in step order (zeros from len on).  The SimHash
+    // directions may start at any float, so the load claims no more than that
+    // (the same 16-byte instruction: device memory serves it at any dword)
     auto dirs4 = [&](const float* dirs, int k, int len, float (&x)[4]) {
         const bool in = FULL || k + 4 * g < len;
-        const float4 v = *reinterpret_cast<const float4*>(dirs + (uint32_t)(ec * len + (in ? k + 4 * g : 0)));
+        const floatx4u v = *reinterpret_cast<const floatx4u*>(dirs + (uint32_t)(ec * len + (in ? k + 4 * g : 0)));
         x[0] = in ? v.x : 0.f;
         x[1] = in ? v.y : 0.f;
         x[2] = in ? v.z : 0.f;

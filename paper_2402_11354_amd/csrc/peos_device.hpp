@@ -7,6 +7,7 @@
 namespace peos {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));  // in memory at any float
 
 constexpr int kWave = 64;
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // empty visited-hash slot
