@@ -419,26 +419,35 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
         wait_norms();
         store(acc[0], 0, t);
     }
-    for (int t = s0; t < s1; t += 4) {
-        floatx4 acc[4];
-        const float* av[4];
-        const float* bv[4];
-        int ti[4], tj[4];
+    // subspace tiles t .. t + N - 1 side by side
+    auto subspace = [&](auto tiles, int t) __attribute__((always_inline)) {
+        constexpr int N = decltype(tiles)::value;
+        floatx4 acc[N];
+        const float* av[N];
+        const float* bv[N];
+        int ti[N], tj[N];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int v = t + u < s1 ? t + u : s1 - 1;  // (a slot past the last repeats it, not stored)
-            ti[u] = v / mt;
-            tj[u] = v - ti[u] * mt;
+        for (int u = 0; u < N; ++u) {
+            ti[u] = (t + u) / mt;
+            tj[u] = (t + u) - ti[u] * mt;
             bv[u] = a.dirs_a + ((int64_t)ti[u] * m + 16 * tj[u]) * dp;
             av[u] = ql + ti[u] * dp;
             acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
-        chains(std::integral_constant<int, 4>(), av, bv, dp, acc);
+        chains(tiles, av, bv, dp, acc);
         wait_norms();
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (t + u < s1) store(acc[u], 1 + ti[u], tj[u]);
+        for (int u = 0; u < N; ++u) store(acc[u], 1 + ti[u], tj[u]);
+    };
+    // (the last one to three tiles as they are: a slot that repeats a tile
+    // costs its loads and MFMAs, three quarters of all at L = 1)
+    int t = s0;
+    for (; t + 4 <= s1; t += 4) subspace(std::integral_constant<int, 4>(), t);
+    if (s1 - t >= 2) {
+        subspace(std::integral_constant<int, 2>(), t);
+        t += 2;
     }
+    if (t < s1) subspace(std::integral_constant<int, 1>(), t);
     wait_norms();
 }
 
