@@ -33,7 +33,8 @@ struct QueryTableArgs {
     const int32_t* perm;   // optional dimension permutation of the test
 };
 
-// One workgroup of kTableWaves waves per tile of 16 queries.  The tile's
+// One workgroup of kTableWaves waves per tile of 16 queries (for m > 16 and few
+// queries several of kWideWaves, see query_table_wide).  The tile's
 // query rows are staged in LDS with coalesced 16-byte loads (row stride
 // d + 4 floats, so the 16 rows x 4 consecutive k an MFMA step reads fall in
 // 64 distinct banks; up to 61 KB at d = 960); the (L+1) x m/16 output tiles
@@ -281,8 +282,8 @@ __device__ __forceinline__ void query_table16(const QueryTableArgs& a, float* qs
     }
 }
 
-// m > 16, staged rows, no permutation: the (L + 1) m / 16 output tiles of a
-// block of 16 queries are dealt to the waves of gridDim.y workgroups by their
+// m > 16, staged rows, no permutation, few queries: the (L + 1) m / 16 output
+// tiles of a block of 16 queries are dealt to the waves of gridDim.y workgroups by their
 // number of K steps (a full-space tile counts as L subspace tiles: it is one
 // chain and is not split), so that a few queries with many directions fill the
 // chip.  Every tile keeps its chain of MFMAs in the order of K, so the table
@@ -451,8 +452,8 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
     wait_norms();
 }
 
-// the three bodies as kernels of their own (each with its own registers)
-enum TableBody { kTable16, kTableWide, kTableGeneral };
+// the bodies as kernels of their own (each with its own registers)
+enum TableBody { kTable16, kTableWide, kTableMany, kTableGeneral };
 
 template <int BODY>
 __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 64,
@@ -519,12 +520,13 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
     const bool rv = row < nrows;
     // this lane's row: in LDS, or in global memory (rows past the batch read
     // row 0 and contribute zeros)
-    const float* qrow = a.staged ? qs + row * ld : a.queries + (q0 + (rv ? row : 0)) * (int64_t)d;
-    auto qget = [&](int kk) { return (a.staged || rv) ? qrow[kk] : 0.f; };
+    const bool staged = BODY == kTableMany || a.staged;
+    const float* qrow = staged ? qs + row * ld : a.queries + (q0 + (rv ? row : 0)) * (int64_t)d;
+    auto qget = [&](int kk) { return (staged || rv) ? qrow[kk] : 0.f; };
     if (wv == 0) {
         // |q| in the order of staged_row_norm, from LDS or global memory
         float nrm;
-        if (a.staged) {
+        if (staged) {
             nrm = staged_row_norm(qrow, d, kq);
         } else {
             float ss = 0.f;
@@ -561,16 +563,33 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
         };
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
         int k0 = 0;
-        for (; k0 + 32 <= k_len; k0 += 32) {
-            float bb[8];
+        if constexpr (BODY == kTableMany) {
+            // staged rows, no permutation, m > 16 and blocks enough to fill the
+            // chip: the wide form's order of K, four groups a round trip
+            const float* ql = qs + row * ld + k_begin;
+            const int ng = k_len >> 4;
+            int j = 0;
+            for (; j + 4 <= ng; j += 4) acc = mfma_groups<4>(acc, ql, bv, j, 4 * kq);
+            switch (ng - j) {
+            case 3: acc = mfma_groups<3>(acc, ql, bv, j, 4 * kq); break;
+            case 2: acc = mfma_groups<2>(acc, ql, bv, j, 4 * kq); break;
+            case 1: acc = mfma_groups<1>(acc, ql, bv, j, 4 * kq); break;
+            default: break;
+            }
+            for (k0 = 16 * ng; k0 < k_len; k0 += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ql[k0 + kq], bv[k0 + kb], acc, 0, 0, 0);
+        } else {
+            for (; k0 + 32 <= k_len; k0 += 32) {
+                float bb[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) bb[u] = bv[k0 + 4 * u + kb];
+                for (int u = 0; u < 8; ++u) bb[u] = bv[k0 + 4 * u + kb];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0 + 4 * u), bb[u], acc, 0, 0, 0);
+                for (int u = 0; u < 8; ++u)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0 + 4 * u), bb[u], acc, 0, 0, 0);
+            }
+            for (; k0 < k_len; k0 += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0), bv[k0 + kb], acc, 0, 0, 0);
         }
-        for (; k0 < k_len; k0 += 4)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0), bv[k0 + kb], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int orow = 4 * (lane >> 4) + r;

@@ -251,6 +251,7 @@ int ensure_kernel_attrs(int dev)
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
         const void* tables[] = {(const void*)peos::k_query_table<peos::kTable16>,
                                 (const void*)peos::k_query_table<peos::kTableWide>,
+                                (const void*)peos::k_query_table<peos::kTableMany>,
                                 (const void*)peos::k_query_table<peos::kTableGeneral>};
         for (const void* f : tables)
             HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
@@ -786,14 +787,38 @@ int peos_query_tables(const peos_index* ix, const float* queries, int64_t nq, fl
     if (rc) return rc;
     const dim3 block(64 * peos::kTableWaves);
     hipStream_t s = (hipStream_t)stream;
+    // m > 16.  Up to two blocks of 16 queries a CU, which is what is resident
+    // of the wide form's workgroups, its tiles are spread over the chip.  With
+    // more blocks the chip is full without that, and for short chains (blocks
+    // below 64 coordinates, or fewer than four direction tiles) a workgroup of
+    // four waves and no lane permutes does a block in less: it is taken while
+    // its workgroups (`fit` a CU by LDS, eight by registers) are resident at
+    // once, and always where seven or more fit (d <= 361); elsewhere the wide
+    // form's 64-byte reads of long rows win.  Microseconds, wide / many:
+    // d = 128, L = 8, m = 32: 8,192 queries 10.4 / 10.6, 12,000 13.5 / 11.7,
+    // 100,000 68 / 44; d = 640, L = 16, m = 64: 12,000 54.7 / 48.7, 16,384
+    // 65 / 78; d = 256, L = 4, m = 128: 12,000 29.8 / 33.7; d = 960, L = 16,
+    // m = 128: 2,049 39 / 75, 100,000 806 / 1115.
+    const int64_t cus = ix->num_cu;
+    const int64_t fit = std::min<int64_t>(8, ix->lds_per_cu / (int64_t)(lds + 64));
+    const bool many = blocks > 2 * cus && (a.d / a.L < 64 || a.m < 64) && (fit >= 7 || blocks <= fit * cus);
     if (!a.staged || a.perm) {
         hipLaunchKernelGGL(peos::k_query_table<peos::kTableGeneral>, dim3((unsigned)blocks), block, lds, s, a);
     } else if (a.m == 16) {
         hipLaunchKernelGGL(peos::k_query_table<peos::kTable16>, dim3((unsigned)blocks), block, lds, s, a);
+    } else if (many) {
+        // tables that outgrow the 256 MB last-level cache are bound by their
+        // writes, which are faster from five workgroups a CU than from eight
+        // (d = 128, L = 8, m = 128, 100,000 queries: 200 -> 171 us)
+        const int64_t bytes = nq * (a.L + 1) * a.m * (a.half_out ? 2 : 4);
+        const size_t five = (size_t)(ix->lds_per_cu / 6 + 256);
+        hipLaunchKernelGGL(peos::k_query_table<peos::kTableMany>, dim3((unsigned)blocks), block,
+                           bytes > (256ll << 20) ? std::max(lds, five) : lds, s, a);
     } else {
         // as many workgroups per 16 queries as are resident at once (two a
-        // CU at d = 960), each wave with at least a full-space tile's work
-        const int64_t want = 2 * (int64_t)ix->num_cu / blocks;
+        // CU), each wave with a full-space tile's K steps (with half of them
+        // or more where m / 16 is not a multiple of 4)
+        const int64_t want = 2 * cus / blocks;
         const int64_t most = (2 * (int64_t)(a.m / 16) + peos::kWideWaves - 1) / peos::kWideWaves;
         const unsigned split = (unsigned)std::max<int64_t>(1, std::min(want, most));
         hipLaunchKernelGGL(peos::k_query_table<peos::kTableWide>, dim3((unsigned)blocks, split),

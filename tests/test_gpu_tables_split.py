@@ -54,3 +54,13 @@ def check(d, L, m, nq, flags=0):
                                    (12, 1, 128)])
 def test_tables_of_leftover_tiles(d, L, m, nq):
     check(d, L, m, nq)
+
+
+# (more than 8,192 queries fill the chip without the tiles being dealt out;
+# 45,000 of 9 x 128 floats outgrow the last-level cache)
+@pytest.mark.parametrize("d,L,m,nq,flags", [(128, 8, 32, 8193, 0), (20, 5, 48, 8205, 0), (4, 1, 32, 9000, 0),
+                                            (128, 8, 32, 8200, P.PEOS_FLAG_FP16), (256, 4, 48, 8301, 0),
+                                            (128, 8, 64, 8192, 0), (64, 8, 128, 60_001, 0), (400, 5, 32, 24_600, 0),
+                                            (400, 5, 32, 16_000, 0), (640, 16, 32, 12_300, 0), (256, 4, 64, 8_300, 0)])
+def test_tables_of_many_queries(d, L, m, nq, flags):
+    check(d, L, m, nq, flags)
