@@ -521,17 +521,16 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
     // this lane's row: in LDS, or in global memory (rows past the batch read
     // row 0 and contribute zeros)
     const bool staged = BODY == kTableMany || a.staged;
-    const float* qrow = staged ? qs + row * ld : a.queries + (q0 + (rv ? row : 0)) * (int64_t)d;
-    auto qget = [&](int kk) { return (staged || rv) ? qrow[kk] : 0.f; };
+    const float* qglobal = a.queries + (q0 + (rv ? row : 0)) * (int64_t)d;
     if (wv == 0) {
         // |q| in the order of staged_row_norm, from LDS or global memory
         float nrm;
         if (staged) {
-            nrm = staged_row_norm(qrow, d, kq);
+            nrm = staged_row_norm(qs + row * ld, d, kq);
         } else {
             float ss = 0.f;
             for (int k = kq; k < d; k += 4) {
-                const float v = qget(k);
+                const float v = rv ? qglobal[k] : 0.f;
                 ss = fmaf(v, v, ss);
             }
             ss += __shfl_xor(ss, 16, kWave);
@@ -556,11 +555,6 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
         const int k_len = (i == 0) ? d : dp;
         const float* bv = (i == 0) ? a.dirs_b + (int64_t)jdir * d
                                    : a.dirs_a + ((int64_t)(i - 1) * m + jdir) * dp;
-        // operand k of this lane: coordinate k_begin + k of the (permuted) row
-        auto qa = [&](int k) {
-            const int kk = k_begin + k + kq;
-            return qget(a.perm ? a.perm[kk] : kk);
-        };
         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
         int k0 = 0;
         if constexpr (BODY == kTableMany) {
@@ -579,16 +573,39 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
             for (k0 = 16 * ng; k0 < k_len; k0 += 4)
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ql[k0 + kq], bv[k0 + kb], acc, 0, 0, 0);
         } else {
-            for (; k0 + 32 <= k_len; k0 += 32) {
-                float bb[8];
+            // N steps from k: every load of a kind before the next kind's, as
+            // straight-line code (coordinate k_begin + k of the permuted row;
+            // rows past the batch in global memory are dropped after the load).
+            // What bounds this body is the latency of these loads: with a
+            // branch around each it took 81 us for 17 queries at d = 1,024,
+            // m = 16 (now 66) and 53 for 2,049 permuted ones at d = 960 (31)
+            auto steps = [&](auto count, int k) {
+                constexpr int N = decltype(count)::value;
+                int kk[N];
+                float bb[N], aa[N];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) bb[u] = bv[k0 + 4 * u + kb];
+                for (int u = 0; u < N; ++u) bb[u] = bv[k + 4 * u + kb];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0 + 4 * u), bb[u], acc, 0, 0, 0);
-            }
-            for (; k0 < k_len; k0 += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(qa(k0), bv[k0 + kb], acc, 0, 0, 0);
+                for (int u = 0; u < N; ++u) kk[u] = k_begin + k + 4 * u + kq;
+                if (a.perm) {
+#pragma unroll
+                    for (int u = 0; u < N; ++u) kk[u] = a.perm[kk[u]];
+                }
+                if (staged) {
+                    const float* ql = qs + row * ld;  // (an LDS pointer, so LDS reads)
+#pragma unroll
+                    for (int u = 0; u < N; ++u) aa[u] = ql[kk[u]];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < N; ++u) aa[u] = qglobal[kk[u]];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) aa[u] = rv ? aa[u] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(aa[u], bb[u], acc, 0, 0, 0);
+            };
+            for (; k0 + 32 <= k_len; k0 += 32) steps(std::integral_constant<int, 8>(), k0);
+            for (; k0 < k_len; k0 += 4) steps(std::integral_constant<int, 1>(), k0);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

@@ -18,14 +18,16 @@ def T(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(torch.device("cuda:0"))
 
 
-def check(d, L, m, nq, flags=0):
+def check(d, L, m, nq, flags=0, perm=False):
     rng = np.random.default_rng([d, L, m, nq])
     x = rng.normal(size=(40, d)).astype(np.float32)
     g = ((np.arange(40)[:, None] + np.arange(1, 5)[None, :]) % 40).astype(np.int32)
     A = rng.normal(size=(L, m, d // L)).astype(np.float32)
     B = rng.normal(size=(m, d)).astype(np.float32)
     q = (rng.normal(size=(nq, d)) * 3).astype(np.float32)
-    idx = P.peos_build_tables(T(x), T(g), 0, L, m, T(A), T(B), P.PEOS_METRIC_L2, flags=flags)
+    p = rng.permutation(d).astype(np.int32) if perm else np.arange(d, dtype=np.int32)
+    idx = P.peos_build_tables(T(x), T(g), 0, L, m, T(A), T(B), P.PEOS_METRIC_L2, flags=flags,
+                              perm=T(p) if perm else None)
 
     def tables(rows):
         out = torch.full((len(rows), L + 1, m), np.nan, device="cuda:0",
@@ -39,7 +41,7 @@ def check(d, L, m, nq, flags=0):
     out, norms = tables(q)
     assert not np.isnan(out).any()
     pick = np.unique(np.linspace(0, nq - 1, 40).astype(int))
-    ref = np.stack([O.query_table(q[i], L, m, A, B) for i in pick])
+    ref = np.stack([O.query_table(q[i][p], L, m, A, B) for i in pick])
     if flags & P.PEOS_FLAG_FP16:  # half an ulp of the half, on top
         np.testing.assert_allclose(out[pick], ref, rtol=2.0 ** -11, atol=2e-5)
     else:
@@ -64,3 +66,16 @@ def test_tables_of_leftover_tiles(d, L, m, nq):
                                             (400, 5, 32, 16_000, 0), (640, 16, 32, 12_300, 0), (256, 4, 64, 8_300, 0)])
 def test_tables_of_many_queries(d, L, m, nq, flags):
     check(d, L, m, nq, flags)
+
+
+# rows too long to be staged, and a permutation of the coordinates: the general
+# form, with and without steps past whole groups of eight
+@pytest.mark.parametrize("perm", [False, True])
+@pytest.mark.parametrize("d,L,m,nq", [(1024, 16, 16, 35), (1040, 4, 48, 3), (1036, 1, 16, 16), (2048, 32, 32, 17)])
+def test_tables_of_unstaged_rows(d, L, m, nq, perm):
+    check(d, L, m, nq, perm=perm)
+
+
+@pytest.mark.parametrize("d,L,m,nq", [(128, 8, 16, 35), (20, 5, 48, 7), (900, 3, 32, 18), (4, 1, 16, 1)])
+def test_tables_of_permuted_rows(d, L, m, nq):
+    check(d, L, m, nq, perm=True)
