@@ -75,7 +75,7 @@ struct EdgeBuildArgs {
                           // the test's vectors is original coordinate perm[k]
     const float* sdirs;   // 64 x d SimHash vectors, or null
     int64_t sig_off;      // SimHash signatures within a record
-    int unit_nodes;       // nodes per wave: max(1, 64 / R)
+    int unit_nodes;       // nodes per wave: 1 .. max(1, 64 / R)
 };
 
 constexpr int kCompactZeroEdge = 255;
@@ -306,8 +306,20 @@ __global__ __launch_bounds__(64, MT <= 2 ? 4 : 3) void k_edge_build(EdgeBuildArg
         }
     };
 
+    // tiles of 16 edges; one without an edge (sparse rows, small graphs) gets
+    // its zero records here
+    const uint64_t present = ballot(lane < E && (uint32_t)row[lane] < (uint64_t)a.n);
+    if (lane < E && ((present >> (lane & 48)) & 0xFFFFu) == 0) {
+        const int b = node_of(lane), j = lane - b * R;
+        uint8_t* rv = a.rec + (v0 + b) * a.node_stride;
+        uint32_t* codes = reinterpret_cast<uint32_t*>(rv + a.codes_off + (int64_t)j * cbytes);
+        for (int w = 0; w < cbytes >> 2; ++w) codes[w] = 0u;
+        if (SIM) *reinterpret_cast<uint2*>(rv + a.sig_off + 8 * j) = make_uint2(0u, 0u);
+        ei[lane] = COMPACT ? 0 : -1;
+    }
     const int ntile = (E + 15) >> 4;
     for (int T = 0; T < ntile; ++T) {
+        if (((present >> (16 * T)) & 0xFFFFu) == 0) continue;
         const int f = 16 * T + ec;
         int32_t u = f < E ? row[f] : -1;
         if (u >= a.n) u = -1;  // never dereferenced (reported through err)

@@ -634,7 +634,12 @@ int peos_build_tables_ex(const float* base, int64_t n, int32_t d, const int32_t*
     a.perm = perm;
     a.sdirs = (flags & PEOS_FLAG_SIMHASH) ? sdirs : nullptr;
     a.sig_off = l.sig_off;
+    // whole nodes of up to 64 edges a wave (full tiles of 16 edges, one edge a
+    // lane at the end), fewer nodes while the chip has room for more waves:
+    // a small build is the chain of one wave's tiles
     a.unit_nodes = R < 64 ? 64 / R : 1;
+    while (a.unit_nodes > 1 && (n + a.unit_nodes - 1) / a.unit_nodes < 2 * di.num_cu)
+        a.unit_nodes = (a.unit_nodes + 1) / 2;
     launch_edge_build(a, (flags & PEOS_FLAG_COMPACT) != 0, s);
     HIP_TRY(hipGetLastError());
     const int64_t bf16_off = (flags & PEOS_FLAG_BF16_BASE) ? round_up(n * l.stride, 256) : 0;
