@@ -51,6 +51,14 @@ constexpr int kVariantLong = 16;
 constexpr int kBufferRsrcWord3 = 0x00020000;
 constexpr int kCompactLutBins = 256;
 
+// the bin of A in the quantile table: every lane reads its bin, also one whose A
+// is not in (0, 1) and discards it, so the bounds are kept before the conversion
+// (NaN: bin 0)
+__host__ __device__ __forceinline__ int compact_bin(float A)
+{
+    return (int)fminf(fmaxf(A * (float)kCompactLutBins, 0.f), (float)(kCompactLutBins - 1));
+}
+
 struct SearchArgs {
     const float* base;
     const uint16_t* base16;  // bfloat16 copy of the base (kFlagBf16Base)
@@ -894,12 +902,10 @@ __global__ __launch_bounds__(kMaxWavesPerQuery * 64,
 #pragma unroll
                         for (int i = 1; i <= 4; ++i)  // zero entries past L
                             h += tab[(int)((cw[0] >> ((i - 1) * 8)) & 0xFFu) * TW + i];
-                        int b = (int)(A * (float)kCompactLutBins);
-                        b = b < 0 ? 0 : (b < kCompactLutBins - 1 ? b : kCompactLutBins - 1);
                         const bool zero = ci == 255u;
                         const bool ge1 = !zero & (A >= 1.f), le0 = !zero & !ge1 & (A <= 0.f);
                         kind = zero ? 0 : (ge1 ? 1 : (le0 ? 2 : 3));
-                        const bool hpass = h >= a.aux[b];
+                        const bool hpass = h >= a.aux[compact_bin(A)];
                         pass = zero ? diff < 0.f : (ge1 ? false : (le0 ? true : hpass));
                     } else {
                         // full precision: sg = g_e, se = |e|; halves: sg =
