@@ -516,7 +516,9 @@ int peos_serve_submit(peos_server* server, const float* queries, int32_t nq, int
 /* Progress: collect finished batches (their requests' results are copied
  * out), issue waiting requests on free slots, and return up to max_done
  * tickets of completed requests in done (host), their count in *n_done.
- * wait != 0: if nothing has completed, block until a batch in flight does.  Errors: PEOS_EINVAL, PEOS_EHIP. */
+ * wait != 0: if nothing has completed, wait until a batch in flight (any of
+ * them) does; after the first 50 us the thread sleeps most of the wait.
+ * Errors: PEOS_EINVAL, PEOS_EHIP. */
 int peos_serve_poll(peos_server* server, int32_t wait, uint64_t* done, int32_t max_done,
                     int32_t* n_done);
 /* Eight counters (host int64): launches, requests completed, queries

@@ -16,6 +16,7 @@
 // depend on how requests are batched.
 #pragma once
 
+#include <chrono>
 #include <deque>
 #include <thread>
 #include <vector>
@@ -114,6 +115,30 @@ int serve_reap(peos_server* sv, bool* any)
         if (e != hipSuccess) return fail(PEOS_EHIP, "hipEventQuery: %s", hipGetErrorString(e));
         serve_complete(sv, s);
         *any = true;
+    }
+    return PEOS_OK;
+}
+
+// until any batch in flight is done, whichever slot it is in: its slot takes the
+// requests that wait (blocking on one slot's event left the other slots empty
+// behind a long batch; it also holds the core, since the runtime spins for an
+// event even where it was created to block).  The slots are watched without a
+// pause for kServeSpin, about what waking a sleeping thread takes, then after
+// sleeps of a thirty-second of the time waited, so that a long wait leaves the
+// core to others and a batch is seen at most that much late.
+constexpr std::chrono::microseconds kServeSpin(50), kServeNapMin(10), kServeNapMax(200);
+
+int serve_wait(peos_server* sv)
+{
+    bool busy = false, any = false;
+    for (const ServeSlot& s : sv->slots) busy |= s.busy;
+    const auto start = std::chrono::steady_clock::now();
+    while (busy) {
+        const int rc = serve_reap(sv, &any);
+        if (rc || any) return rc;
+        const auto waited = std::chrono::duration_cast<std::chrono::microseconds>(std::chrono::steady_clock::now() - start);
+        if (waited < kServeSpin) std::this_thread::yield();
+        else std::this_thread::sleep_for(std::min(std::max(waited / 32, kServeNapMin), kServeNapMax));
     }
     return PEOS_OK;
 }
@@ -342,16 +367,8 @@ int peos_serve_poll(peos_server* sv, int32_t wait, uint64_t* done, int32_t max_d
     int rc = serve_reap(sv, &any);
     if (rc) return rc;
     if (wait && !any && sv->finished.empty()) {
-        // until any batch in flight is done, whichever slot it is in: its
-        // slot takes the requests that wait (blocking on one slot's event
-        // left the other slots empty behind a long batch)
-        bool busy = false;
-        for (const ServeSlot& s : sv->slots) busy |= s.busy;
-        while (busy && !any) {
-            rc = serve_reap(sv, &any);
-            if (rc) return rc;
-            if (!any) std::this_thread::yield();
-        }
+        rc = serve_wait(sv);
+        if (rc) return rc;
     }
     rc = serve_dispatch(sv);
     if (rc) return rc;
