@@ -167,6 +167,8 @@ typedef struct {
  * Errors: PEOS_EINVAL if n < 1, d < 1, R < 1, L < 1, d % L != 0, d/L % 4 != 0,
  * m < 16, m % 16 != 0, 2*m > 256, an unknown flag, PEOS_FLAG_COMPACT with
  * L > 4 or with PEOS_FLAG_FP16 / PEOS_FLAG_SIMHASH, or a null output pointer.
+ * d has no upper limit here or in the build; a search needs its query, table
+ * and list within 64 KB of LDS (PEOS_EINVAL).
  */
 int peos_index_bytes(int64_t n, int32_t d, int32_t R, int32_t L, int32_t m, int32_t flags,
                      size_t* index_bytes, size_t* build_ws_bytes);
