@@ -48,9 +48,13 @@
 // gathered again for the residual.
 // Measured: 400,000 nodes of degree 32 at d = 128, L = 8, m = 16 (no perm)
 // 86.8 -> 3.1 ms (one fma per operand load before; now the vector ALUs are
-// busy half the time, the matrix cores 22%, and a wave waits on its gather
-// 44% of its cycles at 3 waves a SIMD); 20,000 nodes at d = 960, L = 16 27.9
-// -> 2.2 ms (55% waiting: two passes over 17 KB segments at 2 waves a SIMD).
+// busy 51% of the time, the matrix cores 22%, and a wave waits 44% of its
+// cycles at 2.9 waves a SIMD); 20,000 nodes at d = 960, L = 16 27.9 -> 2.2 ms
+// (55% waiting: two passes over segments of 240 coordinates, 20 KB of LDS, at
+// 1.8 waves a SIMD).  The general instantiations (MT = 8, blocks one at a time,
+// a coordinate at a time with a permutation), 100,000 nodes of the first shape:
+// with a permutation 21.3 -> 1.6 ms, with SimHash signatures 31.8 -> 2.4 ms;
+// 50,000 at m = 128 89 -> 1.9 ms.
 #pragma once
 
 #include <type_traits>
@@ -58,7 +62,6 @@
 #include "peos_device.hpp"
 
 namespace peos {
-
 
 struct EdgeBuildArgs {
     const float* base;
@@ -81,10 +84,10 @@ struct EdgeBuildArgs {
 constexpr int kCompactZeroEdge = 255;
 // Coordinates of the 16 edges' vectors held in LDS at a time (a multiple of 16,
 // so that every coordinate keeps its place mod 16): vectors of up to 256 are
-// held whole and gathered once, 9 KB a wave at d = 128 and so 13 waves a CU;
-// longer ones go by whole groups of four blocks, around 256 coordinates (17 KB,
-// eight waves a CU), when a group is at most 512, else by 256 wherever the
-// blocks lie.
+// held whole and gathered once (11.6 KB a wave at d = 128, L = 8, so 14 waves a
+// CU; 20.3 KB at d = 256); longer ones go by whole groups of four blocks, as
+// many as make 256 coordinates at most (20 KB, eight waves a CU, at d = 960,
+// L = 16) or one of up to 512 (37 KB), else by 256 wherever the blocks lie.
 constexpr int kSegment = 256;
 constexpr int kMaxGroup = 512;
 constexpr int kChunkWords = 4 * 64 + 16;  // LDS words of 16 coordinates: four steps of 64

@@ -19,7 +19,6 @@
 
 namespace peos {
 
-
 struct QueryTableArgs {
     const float* queries;  // nq x d
     const float* dirs_a;   // L x m x dp

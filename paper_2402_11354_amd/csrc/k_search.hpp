@@ -24,12 +24,13 @@
 //   the list's next entry decide the next v.
 //
 // What one expansion costs (cycles of a wave at 2.4 GHz, measured phase by
-// phase; 1M x 128, ef = 64, one query alone / 10,000 at once): loads and
-// visited set 460 / 540, merge and pop 1270 / 1570, wait for the ids 30 / 230,
-// filter and test 1170 / 1420, gather 2210 / 4200, next node 460 / 570.  With
-// the merge and the pop before the loads, and lists in LDS compared entry by
-// entry, the chain was 207 us for one query of 78 expansions (188 now), 1.26
-// ms for 10,000 (1.16) and 2.95 ms for 4,000 at k = 100, ef = 200 (2.38).
+// phase on a copy with timestamps; 1M x 128, ef = 64, one query alone / 10,000
+// at once): loads and visited set 490 / 580, merge and pop 1230 / 1520, wait for
+// the ids 40 / 190, filter and test 1190 / 1440, gather 2220 / 4180, the rest
+// 550 / 680.  Whole calls with the merge and the pop before the loads and lists
+// in LDS compared entry by entry took 231 us for one query of 78 expansions (208
+// now), 1.25 ms for 10,000 (1.15) and 3.00 ms for 4,000 at k = 100, ef = 200,
+// m = 128 (2.44), both on one GPU.
 #pragma once
 
 #include <type_traits>
@@ -419,7 +420,7 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, int off, u
 }
 
 // REGL: the candidate list is the result list alone (capacity = ef <= 64,
-// the HNSW stopping rule): entry i lives in lane i's registers (rd, ri), so
+// the HNSW stopping rule): entry i lives in lane i's registers (re), so
 // the pop is a ballot and the merge a register scatter through LDS staging.
 template <int MAXL, int FLAGS, bool REGL>
 __global__ __launch_bounds__(kMaxWavesPerQuery * 64,

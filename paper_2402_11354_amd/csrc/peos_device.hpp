@@ -125,19 +125,6 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// sum within aligned groups of G lanes (G a power of two <= 64)
-template <int G>
-__device__ __forceinline__ float group_sum(float v)
-{
-    if (G >= 64) v += xor_lane<32>(v);
-    if (G >= 32) v += xor_lane<16>(v);
-    if (G >= 16) v += xor_lane<8>(v);
-    if (G >= 8) v += xor_lane<4>(v);
-    if (G >= 4) v += xor_lane<2>(v);
-    if (G >= 2) v += xor_lane<1>(v);
-    return v;
-}
-
 // total order on (distance, id): map a float to an unsigned key that sorts
 // like the float (negative values reversed), then append the id.
 __device__ __forceinline__ uint32_t order_bits(float f)
