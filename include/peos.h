@@ -519,7 +519,7 @@ int peos_serve_submit(peos_server* server, const float* queries, int32_t nq, int
  * out), issue waiting requests on free slots, and return up to max_done
  * tickets of completed requests in done (host), their count in *n_done.
  * wait != 0: if nothing has completed, wait until a batch in flight (any of
- * them) does; after the first 50 us the thread sleeps most of the wait.
+ * them) does; after the first 2 ms the thread sleeps most of the wait.
  * Errors: PEOS_EINVAL, PEOS_EHIP. */
 int peos_serve_poll(peos_server* server, int32_t wait, uint64_t* done, int32_t max_done,
                     int32_t* n_done);
