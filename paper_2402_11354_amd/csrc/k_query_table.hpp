@@ -296,6 +296,14 @@ __device__ __forceinline__ void query_table16(const QueryTableArgs& a, float* qs
 // 2,049 queries there: 65 us with one workgroup per 16 queries and a load's
 // latency before every 16 MFMAs, 37 us with the tiles dealt out, 33 us with
 // 64 bytes of a direction by four lanes.
+// ROWS (m < 64, d >= 512): a direction by each lane of 16 instead, as the matrix
+// cores take it.  With two or three direction tiles there are too few chains for
+// the caches to bound them, and the permutes stand in each long one's way: 2,049
+// queries at d = 960, L = 16, m = 32 19.8 -> 17.6 us, one query at L = 1 13.5 ->
+// 12.1.  With more tiles it is the other way (m = 64, d = 512, L = 8: 15.1 with
+// the permutes, 16.0 without), and with short rows too (m = 48, d = 32, L = 4, 300
+// queries: 5.8 and 6.6).
+template <bool ROWS>
 __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const float* qs, float* inv_norm,
                                                  int nrows, int64_t q0, int wv, int lane)
 {
@@ -305,6 +313,7 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
     const int row = lane & 15;
     const int kq = lane >> 4;
     const float* ql = qs + row * (d + 4);
+    const int lrow = ROWS ? row : lane >> 2, lk = 4 * (ROWS ? kq : lane & 3);  // this lane's part of a load
 
     if (wv == 0) {
         const float nrm = staged_row_norm(ql, d, kq);
@@ -349,8 +358,8 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
             for (int j = 0; j < G; ++j)
 #pragma unroll
                 for (int u = 0; u < N; ++u)
-                    b[j][u] = *reinterpret_cast<const float4*>(bv[u] + (lane >> 2) * len +
-                                                               16 * (g + j < ng ? g + j : ng - 1) + 4 * (lane & 3));
+                    b[j][u] = *reinterpret_cast<const float4*>(bv[u] + lrow * len +
+                                                               16 * (g + j < ng ? g + j : ng - 1) + lk);
         };
         // n groups from g on (all operands first, then the MFMAs)
         auto mul = [&](float4 (&b)[G][N], int g, int n) __attribute__((always_inline)) {
@@ -359,7 +368,7 @@ __device__ __forceinline__ void query_table_wide(const QueryTableArgs& a, const 
             for (int j = 0; j < G; ++j)
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
-                    b[j][u] = by_row(b[j][u]);
+                    if (!ROWS) b[j][u] = by_row(b[j][u]);
                     aq[j][u] = *reinterpret_cast<const float4*>(av[u] + 16 * (g + j < ng ? g + j : ng - 1) + 4 * kq);
                 }
 #pragma unroll
@@ -510,7 +519,8 @@ __global__ __launch_bounds__((BODY == kTableWide ? kWideWaves : kTableWaves) * 6
         return;
     }
     if constexpr (BODY == kTableWide) {
-        query_table_wide(a, qs, inv_norm, nrows, q0, wv, lane);
+        if (m < 64 && d >= 512) query_table_wide<true>(a, qs, inv_norm, nrows, q0, wv, lane);
+        else query_table_wide<false>(a, qs, inv_norm, nrows, q0, wv, lane);
         return;
     }
 
